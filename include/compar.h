@@ -16,7 +16,7 @@
  * matrices (the paper's matrix-multiplication interface of Sec. 2.1, in BLAS
  * form), with four hand-written HIP variants for gfx950 registered by cmp_init:
  *
- *   id 0 "f32_simt"  FP32 FMA on the vector ALUs            stated bound 1e-5
+ *   id 0 "f32_simt"  FP32 FMA chains (FP32 MFMA)             stated bound 1e-5
  *   id 1 "bf16x3"    bf16 hi/lo split, three MFMA products  stated bound 1e-5
  *   id 2 "fp8r"      E4M3 + one residual pass, four MFMA
  *                    products with per-128x128-tile scales  stated bound 1e-3

@@ -1,38 +1,35 @@
-// FP32 SIMT GEMM for gfx950: C = alpha * A * B + beta * C, row-major, any
-// shape and leading dimension.  The plain-precision variant of the "gemm"
-// interface: every product and sum is an FP32 FMA on the vector ALUs.
+// FP32 GEMM for gfx950 (the "f32_simt" variant): C = alpha * A * B + beta * C,
+// row-major, any shape and leading dimension, every product and sum an FP32 FMA.
 //
-// Two launch forms share the tile code of simt_tile.h:
+// Two launch forms share the tile code of f32_tile.h:
 //   - one problem: a tile per workgroup, tiles renumbered so each XCD works
-//     on a contiguous, L2-friendly block of C.  The tile is the largest of
-//     128 x 256, 128 x 128, 64 x 128 and 64 x 64 (K step 16) that still gives
-//     every CU two tiles (the smallest when none does): on MI355X a 128 x 256
-//     tile streams 91-93 TFLOP/s at 4096^2..8192^2 against 81-87 for
-//     128 x 128, and at 2048^2 64 x 128 tiles (512 of them) 58 against 42;
+//     on a contiguous, L2-friendly block of C;
 //   - a group of problems of uneven shapes: one persistent launch whose
 //     workgroups claim tiles of the concatenated tile list of all problems
 //     from a counter as they go (problems sorted by decreasing K, so the
 //     longest tiles go first and the tail is short), with the tile shape
 //     picked per group by the autotuner from kGroupedConfigs.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
-#include "simt_tile.h"
+#include "f32_tile.h"
 
 namespace cmp {
 namespace {
 
-using CfgL = SimtCfg<128, 256, 16, 8, 16>;
-using Cfg128 = SimtCfg<128, 128, 16, 8, 8>;
-using CfgM = SimtCfg<64, 128, 16, 4, 8>;
-using CfgS = SimtCfg<64, 64, 16, 4, 4>;
+using CfgL = F32Cfg<128, 256, 16, 32, 2>;
+using CfgD = F32Cfg<128, 128, 32, 32, 2>;
+using CfgM = F32Cfg<64, 64, 16, 32, 4>;
+using CfgS = F32Cfg<32, 32, 64, 16, 2>;
 
-template <typename Cfg, bool VEC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gemm_f32_simt_kernel(
-    SimtProblem p, int tiles_m, int tiles_n) {
-    __shared__ __attribute__((aligned(16))) float smem[Cfg::SMEM_FLOATS];
+template <typename Cfg, int WAVES>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) void gemm_f32_kernel(
+    F32Problem p, bool vec, int tiles_m, int tiles_n) {
+    __shared__ __attribute__((aligned(256))) float smem[Cfg::SMEM_FLOATS];
     int tm, tn;
     grouped_tile(xcd_remap(blockIdx.x, tiles_m * tiles_n), tiles_m, tiles_n, 8, tm, tn);
-    simt_tile<Cfg, VEC>(p, (int64_t)tm * Cfg::BM, (int64_t)tn * Cfg::BN, smem);
+    f32_tile<Cfg>(p, (int64_t)tm * Cfg::BM, (int64_t)tn * Cfg::BN, vec, smem);
 }
 
 // Persistent grouped kernel over the concatenated tile list (tile_start[p] is
@@ -49,7 +46,7 @@ __global__ void grouped_reset_kernel(unsigned* counter) {
 template <typename Cfg>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gemm_f32_grouped_kernel(
     const GroupedDesc* __restrict__ desc, int count, int total_tiles, unsigned* __restrict__ counter) {
-    __shared__ __attribute__((aligned(16))) float smem[Cfg::SMEM_FLOATS];
+    __shared__ __attribute__((aligned(256))) float smem[Cfg::SMEM_FLOATS];
     __shared__ int next_tile;
     for (int tile = blockIdx.x; tile < total_tiles;) {
         // last problem whose first tile is <= tile (binary search, wave-uniform)
@@ -64,13 +61,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
         const int tiles_n = dg[lo].tiles_n;
         const int local = tile - dg[lo].tile_start;
         const int tm = local / tiles_n, tn = local - (local / tiles_n) * tiles_n;
-        const SimtProblem p{dg[lo].M, dg[lo].N, dg[lo].K, dg[lo].lda, dg[lo].ldb, dg[lo].ldc,
+        const F32Problem p{dg[lo].M, dg[lo].N, dg[lo].K, dg[lo].lda, dg[lo].ldb, dg[lo].ldc,
                             dg[lo].alpha, dg[lo].beta, dg[lo].A, dg[lo].B, dg[lo].C};
-        const bool vec = dg[lo].vec != 0;
-        if (vec)
-            simt_tile<Cfg, true>(p, (int64_t)tm * Cfg::BM, (int64_t)tn * Cfg::BN, smem);
-        else
-            simt_tile<Cfg, false>(p, (int64_t)tm * Cfg::BM, (int64_t)tn * Cfg::BN, smem);
+        f32_tile<Cfg>(p, (int64_t)tm * Cfg::BM, (int64_t)tn * Cfg::BN, dg[lo].vec != 0, smem);
         __syncthreads();  // LDS is reused by the next tile; next_tile read by every lane
         if (threadIdx.x == 0) {
             const unsigned ticket = atomicAdd(counter, 1u);
@@ -115,16 +108,16 @@ hipError_t launch_gemm_f32_grouped(int config, const GroupedDesc* desc, int coun
     if (total_tiles <= 0) return hipSuccess;
     if (grid < 1 || grid > total_tiles || !counter) return hipErrorInvalidValue;
     switch (config) {
-        case 0: return launch_grouped_cfg<SimtCfg<64, 64, 16, 4, 4>>(desc, count, total_tiles, grid, counter, stream);
-        case 1: return launch_grouped_cfg<SimtCfg<64, 64, 32, 4, 4>>(desc, count, total_tiles, grid, counter, stream);
-        case 2: return launch_grouped_cfg<SimtCfg<64, 128, 16, 4, 8>>(desc, count, total_tiles, grid, counter, stream);
-        case 3: return launch_grouped_cfg<SimtCfg<128, 64, 16, 8, 4>>(desc, count, total_tiles, grid, counter, stream);
-        case 4: return launch_grouped_cfg<SimtCfg<128, 128, 16, 8, 8>>(desc, count, total_tiles, grid, counter, stream);
-        case 5: return launch_grouped_cfg<SimtCfg<128, 128, 32, 8, 8>>(desc, count, total_tiles, grid, counter, stream);
-        case 6: return launch_grouped_cfg<SimtCfg<256, 128, 16, 16, 8>>(desc, count, total_tiles, grid, counter, stream);
-        case 7: return launch_grouped_cfg<SimtCfg<128, 256, 16, 8, 16>>(desc, count, total_tiles, grid, counter, stream);
-        case 8: return launch_grouped_cfg<SimtCfg<64, 64, 64, 4, 4>>(desc, count, total_tiles, grid, counter, stream);
-        case 9: return launch_grouped_cfg<SimtCfg<64, 128, 64, 4, 8>>(desc, count, total_tiles, grid, counter, stream);
+        case 0: return launch_grouped_cfg<F32Cfg<64, 64, 16, 32, 4>>(desc, count, total_tiles, grid, counter, stream);
+        case 1: return launch_grouped_cfg<F32Cfg<64, 64, 32, 32, 3>>(desc, count, total_tiles, grid, counter, stream);
+        case 2: return launch_grouped_cfg<F32Cfg<64, 128, 16, 32, 3>>(desc, count, total_tiles, grid, counter, stream);
+        case 3: return launch_grouped_cfg<F32Cfg<128, 64, 16, 32, 3>>(desc, count, total_tiles, grid, counter, stream);
+        case 4: return launch_grouped_cfg<F32Cfg<128, 128, 16, 32, 3>>(desc, count, total_tiles, grid, counter, stream);
+        case 5: return launch_grouped_cfg<F32Cfg<128, 128, 32, 32, 2>>(desc, count, total_tiles, grid, counter, stream);
+        case 6: return launch_grouped_cfg<F32Cfg<256, 128, 16, 32, 2>>(desc, count, total_tiles, grid, counter, stream);
+        case 7: return launch_grouped_cfg<F32Cfg<128, 256, 16, 32, 2>>(desc, count, total_tiles, grid, counter, stream);
+        case 8: return launch_grouped_cfg<F32Cfg<64, 64, 64, 32, 2>>(desc, count, total_tiles, grid, counter, stream);
+        case 9: return launch_grouped_cfg<F32Cfg<64, 128, 64, 32, 2>>(desc, count, total_tiles, grid, counter, stream);
         default: return hipErrorInvalidValue;
     }
 }
@@ -133,37 +126,28 @@ int grouped_blocks_per_cu(int config) {
     int nb = 0;
     hipError_t e = hipErrorInvalidValue;
     switch (config) {
-        case 0: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<SimtCfg<64, 64, 16, 4, 4>>, 256, 0); break;
-        case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<SimtCfg<64, 64, 32, 4, 4>>, 256, 0); break;
-        case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<SimtCfg<64, 128, 16, 4, 8>>, 256, 0); break;
-        case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<SimtCfg<128, 64, 16, 8, 4>>, 256, 0); break;
-        case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<SimtCfg<128, 128, 16, 8, 8>>, 256, 0); break;
-        case 5: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<SimtCfg<128, 128, 32, 8, 8>>, 256, 0); break;
-        case 6: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<SimtCfg<256, 128, 16, 16, 8>>, 256, 0); break;
-        case 7: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<SimtCfg<128, 256, 16, 8, 16>>, 256, 0); break;
-        case 8: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<SimtCfg<64, 64, 64, 4, 4>>, 256, 0); break;
-        case 9: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<SimtCfg<64, 128, 64, 4, 8>>, 256, 0); break;
+        case 0: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<F32Cfg<64, 64, 16, 32, 4>>, 256, 0); break;
+        case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<F32Cfg<64, 64, 32, 32, 3>>, 256, 0); break;
+        case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<F32Cfg<64, 128, 16, 32, 3>>, 256, 0); break;
+        case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<F32Cfg<128, 64, 16, 32, 3>>, 256, 0); break;
+        case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<F32Cfg<128, 128, 16, 32, 3>>, 256, 0); break;
+        case 5: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<F32Cfg<128, 128, 32, 32, 2>>, 256, 0); break;
+        case 6: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<F32Cfg<256, 128, 16, 32, 2>>, 256, 0); break;
+        case 7: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<F32Cfg<128, 256, 16, 32, 2>>, 256, 0); break;
+        case 8: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<F32Cfg<64, 64, 64, 32, 2>>, 256, 0); break;
+        case 9: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_grouped_kernel<F32Cfg<64, 128, 64, 32, 2>>, 256, 0); break;
         default: break;
     }
     return (e == hipSuccess && nb > 0) ? nb : 1;
 }
 
-template <typename Cfg>
-hipError_t launch_simt(const SimtProblem& p, bool vec, hipStream_t stream) {
+template <typename Cfg, int WAVES>
+hipError_t launch_f32(const F32Problem& p, bool vec, hipStream_t stream) {
     const int tiles_m = (int)((p.M + Cfg::BM - 1) / Cfg::BM);
     const int tiles_n = (int)((p.N + Cfg::BN - 1) / Cfg::BN);
-    const int nb = tiles_m * tiles_n;
-    if (nb == 0) return hipSuccess;
-    if (vec)
-        hipLaunchKernelGGL((gemm_f32_simt_kernel<Cfg, true>), dim3(nb), dim3(256), 0, stream, p, tiles_m, tiles_n);
-    else
-        hipLaunchKernelGGL((gemm_f32_simt_kernel<Cfg, false>), dim3(nb), dim3(256), 0, stream, p, tiles_m, tiles_n);
+    hipLaunchKernelGGL((gemm_f32_kernel<Cfg, WAVES>), dim3(tiles_m * tiles_n), dim3(256), 0, stream, p, vec, tiles_m,
+                       tiles_n);
     return hipGetLastError();
-}
-
-template <typename Cfg>
-int64_t simt_tiles(int64_t M, int64_t N) {
-    return ((M + Cfg::BM - 1) / Cfg::BM) * ((N + Cfg::BN - 1) / Cfg::BN);
 }
 
 hipError_t launch_gemm_f32_simt(int64_t M, int64_t N, int64_t K, float alpha, const float* A,
@@ -173,12 +157,27 @@ hipError_t launch_gemm_f32_simt(int64_t M, int64_t N, int64_t K, float alpha, co
     const bool vec = (lda % 4 == 0) && (ldb % 4 == 0) &&
                      ((reinterpret_cast<uintptr_t>(A) & 15) == 0) &&
                      ((reinterpret_cast<uintptr_t>(B) & 15) == 0);
-    const SimtProblem p{M, N, K, lda, ldb, ldc, alpha, beta, A, B, C};
-    constexpr int64_t kWant = 2 * 256;   // two tiles for each of the 256 CUs
-    if (simt_tiles<CfgL>(M, N) >= kWant) return launch_simt<CfgL>(p, vec, stream);
-    if (simt_tiles<Cfg128>(M, N) >= kWant) return launch_simt<Cfg128>(p, vec, stream);
-    if (simt_tiles<CfgM>(M, N) >= kWant) return launch_simt<CfgM>(p, vec, stream);
-    return launch_simt<CfgS>(p, vec, stream);
+    const F32Problem p{M, N, K, lda, ldb, ldc, alpha, beta, A, B, C};
+    // The tile with the least expected time.  The CU with the most tiles, n =
+    // ceil(tiles / 256) of them, takes (n + c) * BM * BN / rate (per K): `rate`
+    // is what the tile reaches with many tiles on each CU and c the cost of
+    // filling and draining the pipeline in tiles, both fitted to these
+    // measurements (TFLOP/s, one launch, 5 us of it the launch itself):
+    //               512^3  1024^3  2048^3  4096^3  8192^3  2000x3000x2500
+    //   128 x 256                     67     143     148       88
+    //   128 x 128                    124     143     146       95
+    //    64 x  64       17      75   118     129     134      112
+    //    32 x  32       29      74
+    auto cost = [&](int bm, int bn, double c, double rate) {
+        const double n = (double)((((M + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256);
+        return (n + c) * bm * bn / rate;
+    };
+    const double l = cost(128, 256, 0.1, 150), d = cost(128, 128, 0.19, 148), m = cost(64, 64, 0.35, 130),
+                 q = cost(32, 32, 0.5, 98);
+    if (q <= l && q <= d && q <= m) return launch_f32<CfgS, 4>(p, vec, stream);
+    if (m <= l && m <= d) return launch_f32<CfgM, 4>(p, vec, stream);
+    if (d <= l) return launch_f32<CfgD, 2>(p, vec, stream);
+    return launch_f32<CfgL, 2>(p, vec, stream);
 }
 
 hipError_t launch_scale_c(int64_t M, int64_t N, float beta, float* C, int64_t ldc,

@@ -15,12 +15,12 @@ namespace cmp {
 void host_gemm_f32(int64_t M, int64_t N, int64_t K, float alpha, const float* A, int64_t lda,
                    const float* B, int64_t ldb, float beta, float* C, int64_t ldc, int max_threads);
 
-// ---- FP32 SIMT GEMM (vector-ALU FMA, LDS-staged tiles) -------------------
+// ---- FP32 GEMM (chains of FP32 FMAs on the FP32 MFMA, LDS-staged tiles) ----
 hipError_t launch_gemm_f32_simt(int64_t M, int64_t N, int64_t K, float alpha,
                                 const float* A, int64_t lda, const float* B, int64_t ldb,
                                 float beta, float* C, int64_t ldc, hipStream_t stream);
 
-// Grouped FP32 SIMT launch over many problems of uneven shapes.  The
+// Grouped FP32 launch over many problems of uneven shapes.  The
 // descriptor array (device memory) lists the problems in launch order with
 // the first tile index of each (prefix sum of tiles_m * tiles_n); `grid`
 // persistent workgroups stride over all `total_tiles`.  `vec` marks problems
