@@ -222,14 +222,15 @@ hipError_t launch_rademacher(int64_t n, uint64_t seed, double* x, hipStream_t st
 
 // ---- selector network -------------------------------------------------------
 // Parameters are 4740 floats (see compar.h).  Training runs `steps` Adam steps
-// in one resident workgroup; X, Y standardised (n x 4) device arrays.
+// (two kernels each) over X, Y, standardised (n x 4) device arrays; bias holds
+// 2 * steps doubles of scratch.  grad_out: only the gradient (and the loss), no step.
 constexpr int kMlpParams = 4 * 64 + 64 + 64 * 64 + 64 + 64 * 4 + 4;
 constexpr int kMlpMaxRows = 8192;
 // partial-gradient scratch: one (params + loss) record per 32-row workgroup
 constexpr int kMlpPartFloats = (kMlpMaxRows / 32) * (kMlpParams + 1);
 hipError_t launch_mlp_train(int n, const float* X, const float* Y, float* params, float* m,
-                            float* v, float* part, int steps, int t0, float lr, float* loss_trace,
-                            float* grad_out, hipStream_t stream);
+                            float* v, float* part, int steps, int t0, float lr, double* bias,
+                            float* loss_trace, float* grad_out, hipStream_t stream);
 hipError_t launch_mlp_infer(int n, const float* X, const float* params, float* Y,
                             hipStream_t stream);
 

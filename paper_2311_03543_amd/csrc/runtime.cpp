@@ -2022,16 +2022,17 @@ CMP_API int cmp_mlp_train(cmp_ctx* c, int n, const float* X, const float* Y, int
             Xs[4 * i + j] = (X[4 * i + j] - c->mu_x[j]) / c->sd_x[j];
             Ys[4 * i + j] = (Y[4 * i + j] - c->mu_y[j]) / c->sd_y[j];
         }
-    float* loss_dev = nullptr;
-    if (steps > 0) HIP_TRY(c, hipMalloc(&loss_dev, (size_t)steps * 4));
+    double* bias_dev = nullptr;   // per step: Adam's two bias corrections; then the losses
+    if (steps > 0) HIP_TRY(c, hipMalloc(&bias_dev, (size_t)steps * 20));
+    float* loss_dev = steps > 0 ? (float*)(bias_dev + 2 * (size_t)steps) : nullptr;
     auto cleanup = [&]() {
-        if (loss_dev) (void)hipFree(loss_dev);
+        if (bias_dev) (void)hipFree(bias_dev);
     };
     hipError_t e = hipSuccess;
     if (e == hipSuccess) e = hipMemcpyAsync(d.params, c->mlp_params.data(), kMlpP * 4, hipMemcpyHostToDevice, c->side);
     if (e == hipSuccess) e = hipMemcpyAsync(d.X, Xs.data(), Xs.size() * 4, hipMemcpyHostToDevice, c->side);
     if (e == hipSuccess) e = hipMemcpyAsync(d.Y, Ys.data(), Ys.size() * 4, hipMemcpyHostToDevice, c->side);
-    if (e == hipSuccess) e = cmp::launch_mlp_train(n, d.X, d.Y, d.params, d.m, d.v, d.part, steps, 0, lr, loss_dev, nullptr, c->side);
+    if (e == hipSuccess) e = cmp::launch_mlp_train(n, d.X, d.Y, d.params, d.m, d.v, d.part, steps, 0, lr, bias_dev, loss_dev, nullptr, c->side);
     if (e == hipSuccess) e = hipMemcpyAsync(c->mlp_params.data(), d.params, kMlpP * 4, hipMemcpyDeviceToHost, c->side);
     if (e == hipSuccess && loss_trace && steps > 0)
         e = hipMemcpyAsync(loss_trace, loss_dev, (size_t)steps * 4, hipMemcpyDeviceToHost, c->side);
@@ -2056,7 +2057,7 @@ CMP_API int cmp_mlp_grad(cmp_ctx* c, int n, const float* Xs, const float* Ys, fl
     hipError_t e = hipMemcpyAsync(d.params, c->mlp_params.data(), kMlpP * 4, hipMemcpyHostToDevice, c->side);
     if (e == hipSuccess) e = hipMemcpyAsync(d.X, Xs, 4 * (size_t)n * 4, hipMemcpyHostToDevice, c->side);
     if (e == hipSuccess) e = hipMemcpyAsync(d.Y, Ys, 4 * (size_t)n * 4, hipMemcpyHostToDevice, c->side);
-    if (e == hipSuccess) e = cmp::launch_mlp_train(n, d.X, d.Y, d.params, d.m, d.v, d.part, 0, 0, 0.f, scratch, d.grad, c->side);
+    if (e == hipSuccess) e = cmp::launch_mlp_train(n, d.X, d.Y, d.params, d.m, d.v, d.part, 0, 0, 0.f, nullptr, scratch, d.grad, c->side);
     if (e == hipSuccess) e = hipMemcpyAsync(grad, d.grad, kMlpP * 4, hipMemcpyDeviceToHost, c->side);
     float h = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&h, scratch, 4, hipMemcpyDeviceToHost, c->side);
