@@ -191,6 +191,7 @@ struct cmp_ctx {
     void* hbuf = nullptr;    // pinned host staging of the host variant (A | B | C)
     size_t hbuf_bytes = 0;
     size_t vws_bytes = 0;
+    double* probe_out = nullptr;   // pinned host memory: the residual probe's two sums
     float* mlp_dev = nullptr;  // params | m | v | X | Y | loss | grad | infer io
     hipStream_t side = nullptr;
     // verify mode and fault injection
@@ -1128,15 +1129,15 @@ double verify_threshold(double tol, int64_t M) {
     return tol * (1.0 + 4.0 / std::sqrt(2.0 * (double)std::max<int64_t>(M, 1)));
 }
 
-// Verify workspace: [y: K doubles | pad] [out: 2 doubles | pad] [x: N doubles]
+// Verify workspace: [y: K doubles | pad] [part: 2 per probe workgroup] [x: N doubles]
 // [old C: M x N floats, only when beta != 0]
 struct VLayout {
-    size_t out_d, x_d, c0_b, total_b;
+    size_t part_d, x_d, c0_b, total_b;
 };
 VLayout vlayout(const cmp_gemm_args* a, bool keep_c0) {
     VLayout L;
-    L.out_d = (size_t)round_up(a->K + 2, 32);
-    L.x_d = L.out_d + 32;
+    L.part_d = (size_t)round_up(a->K + 2, 32);
+    L.x_d = L.part_d + 2 * cmp::kFreivaldsBlocks;
     L.c0_b = (size_t)round_up((int64_t)((L.x_d + (size_t)a->N) * 8), 256);
     L.total_b = L.c0_b + (keep_c0 ? (size_t)a->M * (size_t)a->N * 4 : 0);
     return L;
@@ -1148,12 +1149,14 @@ int probe(cmp_ctx* c, const cmp_gemm_args* a, const float* c0, int64_t ldc0, con
           hipStream_t s, double* est) {
     const VLayout L = vlayout(a, false);
     double* base = (double*)c->vws;  // sized by the caller (ensure_vws with vlayout)
-    double* out = base + L.out_d;
+    // the two sums land in pinned host memory: no copy to wait for
+    if (!c->probe_out) HIP_TRY(c, hipHostMalloc((void**)&c->probe_out, 2 * sizeof(double), hipHostMallocDefault));
+    void* out = nullptr;
+    HIP_TRY(c, hipHostGetDevicePointer(&out, c->probe_out, 0));
     HIP_TRY(c, cmp::launch_freivalds(a->M, a->N, a->K, a->alpha, a->A, a->lda, a->B, a->ldb,
-                                     a->beta, c0, ldc0, a->C, a->ldc, x_dev, base, out, s));
-    double h[2];
-    HIP_TRY(c, hipMemcpyAsync(h, out, sizeof h, hipMemcpyDeviceToHost, s));
+                                     a->beta, c0, ldc0, a->C, a->ldc, x_dev, base, base + L.part_d, (double*)out, s));
     HIP_TRY(c, hipStreamSynchronize(s));
+    const volatile double* h = c->probe_out;
     *est = h[1] > 0 ? std::sqrt(h[0]) / std::sqrt(h[1]) : std::sqrt(h[0]);
     return CMP_OK;
 }
@@ -1243,6 +1246,7 @@ CMP_API int cmp_terminate(cmp_ctx* c) {
         if (c->ws) (void)hipFree(c->ws);
         if (c->vws) (void)hipFree(c->vws);
         if (c->hbuf) (void)hipHostFree(c->hbuf);
+        if (c->probe_out) (void)hipHostFree(c->probe_out);
         if (c->mlp_dev) (void)hipFree(c->mlp_dev);
         for (auto& k : c->kpending) {
             (void)hipEventDestroy(k.a);
