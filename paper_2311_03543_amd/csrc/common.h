@@ -99,4 +99,111 @@ __device__ __forceinline__ int paired_kind(int64_t blk, int64_t ta, int64_t tb, 
     return second ? 1 : 0;
 }
 
+// Largest i in [0, count) with start(i) <= value, for non-decreasing starts and
+// start(0) <= value (count >= 1): the problem a workgroup of a grouped launch
+// belongs to.  Every lane of a wave takes part and gets the same answer; a
+// round narrows 64-fold, so 1024 problems take two dependent loads where a
+// binary search takes ten (each 0.5 us or more when another XCD wrote the list).
+template <class F>
+__device__ __forceinline__ int wave_find_last(int count, int value, F&& start) {
+    const int lane = threadIdx.x & 63;
+    int lo = 0, n = count;                        // the answer lies in [lo, lo + n)
+    while (n > 1) {
+        const int step = (n + 63) / 64;
+        const int i = lane * step;                // lane 0 always passes
+        const bool below = i < n && start(lo + i) <= value;
+        const int k = 63 - __builtin_clzll(__ballot(below) | 1ull);
+        lo += k * step;
+        n = n - k * step < step ? n - k * step : step;
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+
+// Tile queues of a persistent grouped launch: the tile list is cut into one
+// list per XCD, tiles [start[x], start[x + 1]), so that the tiles of a problem
+// run on one XCD and read its panels through one L2.  Workgroup b belongs to
+// list b % 8 (the hardware hands consecutive workgroups to the XCDs in turn)
+// and starts with entry b / 8 of it; further entries are claimed from the
+// list's counter, and from the other lists' once the own one is empty.
+// `counters` holds one 32-bit counter per list and one of the workgroups that
+// are done, kQueuePitch words apart, zero before the first launch; the last
+// workgroup zeroes them for the next one (a kernel that did took 4.6 us).
+struct TileQueues {
+    int start[kXcds + 1];
+};
+constexpr int kQueuePitch = 16;                   // 64 bytes: one counter per cache line
+constexpr int kQueueWords = (kXcds + 1) * kQueuePitch;
+
+struct TileClaims {
+    const TileQueues& q;
+    unsigned* counters;
+    int home;
+    unsigned ticket;
+
+    __device__ __forceinline__ TileClaims(const TileQueues& queues, unsigned* c)
+        : q(queues), counters(c), home(blockIdx.x % kXcds), ticket(0) {}
+    __device__ __forceinline__ int size(int x) const { return q.start[x + 1] - q.start[x]; }
+    // entries of list x that workgroups start with
+    __device__ __forceinline__ int started(int x) const {
+        const int wgs = ((int)gridDim.x - x + kXcds - 1) / kXcds;
+        return wgs < size(x) ? wgs : size(x);
+    }
+    // Claim the next entry of the own list (thread 0): the answer arrives under
+    // the current tile.  The opaque zero keeps the compiler from waiting for it here.
+    __device__ __forceinline__ void prefetch() {
+        int zero = 0;
+        asm volatile("" : "+v"(zero));
+        if (threadIdx.x == 0) ticket = atomicAdd(counters + home * kQueuePitch + zero, 1u);
+    }
+    // An entry of any list with one left (the own list first), or -1 when all
+    // are empty.  Wave 0 only; every repetition has seen another list emptied.
+    __device__ __forceinline__ int steal() const {
+        const int lane = threadIdx.x & 63;
+        for (;;) {
+            int x = (home + lane) % kXcds;
+            bool left = false;
+            if (lane < kXcds)
+                left = __hip_atomic_load(counters + x * kQueuePitch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                       (unsigned)(size(x) - started(x));
+            const uint64_t any = __ballot(left);
+            if (!any) return -1;
+            x = (home + (int)__builtin_ctzll(any)) % kXcds;
+            unsigned got = 0;
+            if (lane == 0) got = atomicAdd(counters + x * kQueuePitch, 1u);
+            got = (unsigned)__builtin_amdgcn_readfirstlane((int)got);
+            if (got < (unsigned)(size(x) - started(x))) return q.start[x] + started(x) + (int)got;
+        }
+    }
+    // The workgroup's first tile and its next one (every thread; -1: none left).
+    // `slot` is an LDS word of this object's own.
+    __device__ __forceinline__ int first(int* slot) const {
+        const int i = blockIdx.x / kXcds;
+        if (i < size(home)) return q.start[home] + i;   // uniform
+        return share(slot, threadIdx.x < 64 ? steal() : 0);
+    }
+    __device__ __forceinline__ int next(int* slot) const {
+        int tile = -1;
+        if (threadIdx.x < 64) {
+            const unsigned t = (unsigned)__builtin_amdgcn_readfirstlane((int)ticket);
+            tile = t < (unsigned)(size(home) - started(home)) ? q.start[home] + started(home) + (int)t : steal();
+        }
+        return share(slot, tile);
+    }
+
+    // After the last tile: every claim of this workgroup has been answered.
+    __device__ __forceinline__ void finish() const {
+        if (threadIdx.x == 0 && atomicAdd(counters + kXcds * kQueuePitch, 1u) == gridDim.x - 1)
+            for (int x = 0; x <= kXcds; ++x)
+                __hip_atomic_store(counters + x * kQueuePitch, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+
+  private:
+    __device__ __forceinline__ static int share(int* slot, int tile) {
+        __syncthreads();                          // the last value has been read
+        if (threadIdx.x == 0) *slot = tile;
+        __syncthreads();
+        return __builtin_amdgcn_readfirstlane(*slot);
+    }
+};
+
 }  // namespace cmp

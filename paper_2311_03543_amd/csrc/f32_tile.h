@@ -311,33 +311,41 @@ __device__ __forceinline__ void f32_tile(const F32Problem& p, int64_t m0, int64_
 
     // Epilogue: C = alpha * acc + beta * C (C not read when beta == 0).  Lane l
     // holds column l % MF; rows 8 (r / 4) + 4 (l / 32) + r % 4 of a 32 x 32
-    // block, 4 (l / 16) + r of a 16 x 16 one.
+    // block, 4 (l / 16) + r of a 16 x 16 one.  A block's old values are all
+    // loaded before the first is used; interior tiles check no bounds.
+    const int64_t ldc = p.ldc;
+    const gfloat corner = (gfloat)p.C + (m0 + wm * MF + 4 * fk) * ldc + n0 + wn * MF + fr;
+    auto finish = [&](auto full_tag, auto beta_tag) {
+        constexpr bool FULL = decltype(full_tag)::value, BETA = decltype(beta_tag)::value;
+        const int rl = rows - (wm * MF + 4 * fk), cl = cols - (wn * MF + fr);   // rows and columns from `corner` on
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int64_t col = n0 + (2 * j + wn) * MF + fr;
-            const int64_t row0 = m0 + (2 * i + wm) * MF + 4 * fk;
-            if (col >= p.N) continue;
-            gfloat c = (gfloat)p.C + row0 * p.ldc + col;
-            float old[AR];
-            if (p.beta != 0.f) {
+            for (int j = 0; j < NJ; ++j) {
+                if (!FULL && 2 * j * MF >= cl) continue;
+                const gfloat c = corner + (2 * i * MF * ldc + 2 * j * MF);
+                float old[AR];
+                if (BETA) {
+#pragma unroll
+                    for (int r = 0; r < AR; ++r) {
+                        const int dr = (r >> 2) * 8 + (r & 3);
+                        old[r] = FULL || 2 * i * MF + dr < rl ? c[dr * ldc] : 0.f;
+                    }
+                }
 #pragma unroll
                 for (int r = 0; r < AR; ++r) {
                     const int dr = (r >> 2) * 8 + (r & 3);
-                    old[r] = row0 + dr < p.M ? c[dr * p.ldc] : 0.f;
+                    if (FULL || 2 * i * MF + dr < rl) {
+                        float v = p.alpha * acc[i][j][r];
+                        if (BETA) v = __builtin_fmaf(p.beta, old[r], v);
+                        c[dr * ldc] = v;
+                    }
                 }
             }
-#pragma unroll
-            for (int r = 0; r < AR; ++r) {
-                const int dr = (r >> 2) * 8 + (r & 3);
-                if (row0 + dr < p.M) {
-                    float v = p.alpha * acc[i][j][r];
-                    if (p.beta != 0.f) v = __builtin_fmaf(p.beta, old[r], v);
-                    c[dr * p.ldc] = v;
-                }
-            }
-        }
+    };
+    const bool whole_tile = rows == Cfg::BM && cols == BN;
+    if (p.beta != 0.f) whole_tile ? finish(std::true_type{}, std::true_type{}) : finish(std::false_type{}, std::true_type{});
+    else whole_tile ? finish(std::true_type{}, std::false_type{}) : finish(std::false_type{}, std::false_type{});
 }
 
 }  // namespace cmp

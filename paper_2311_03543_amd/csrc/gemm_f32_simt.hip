@@ -32,47 +32,40 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
     f32_tile<Cfg>(p, (int64_t)tm * Cfg::BM, (int64_t)tn * Cfg::BN, vec, smem);
 }
 
-// Persistent grouped kernel over the concatenated tile list (tile_start[p] is
-// the first tile of problem p; problems come in decreasing order of per-tile
-// work).  Workgroup b starts with tile b; each workgroup that finishes a tile
-// takes the next unclaimed one from the counter (tile grid + ticket), so the
-// list is served greedily in order, longest tiles first.  Every workgroup
-// leaves once a claim passes the end of the list.  The counter must be zero
-// at launch (grouped_reset_kernel runs right before on the same stream).
-__global__ void grouped_reset_kernel(unsigned* counter) {
-    if (threadIdx.x == 0) *counter = 0u;
+// Persistent grouped kernel over the tile lists of `q` (common.h): each
+// workgroup works through tiles, claiming the next one while it computes.  A
+// list holds its pieces in decreasing order of K, so the longest tiles go first.
+// Workgroups per CU a configuration is built for: the LDS of its ring (160 KiB
+// a CU) and the accumulators allow no more.  A tile's fixed costs (first copies
+// from HBM, the stores of C) hide under the other workgroups of the CU.
+template <typename Cfg>
+constexpr int grouped_waves() {
+    constexpr int lds = 160 * 1024 / (Cfg::SMEM_FLOATS * 4 + 256);
+    constexpr int regs = Cfg::MI * Cfg::NJ <= 2 ? 4 : Cfg::MI * Cfg::NJ <= 4 ? 3 : 2;
+    return lds < regs ? lds : regs;
 }
 
 template <typename Cfg>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gemm_f32_grouped_kernel(
-    const GroupedDesc* __restrict__ desc, int count, int total_tiles, unsigned* __restrict__ counter) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(grouped_waves<Cfg>())))
+void gemm_f32_grouped_kernel(const GroupedDesc* __restrict__ desc, int count, TileQueues q,
+                             unsigned* __restrict__ counters) {
     __shared__ __attribute__((aligned(256))) float smem[Cfg::SMEM_FLOATS];
-    __shared__ int next_tile;
-    for (int tile = blockIdx.x; tile < total_tiles;) {
-        // last problem whose first tile is <= tile (binary search, wave-uniform)
-        typedef const __attribute__((address_space(1))) GroupedDesc* gdesc;
-        const gdesc dg = (gdesc)desc;
-        int lo = 0, hi = count - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (dg[mid].tile_start <= tile) lo = mid;
-            else hi = mid - 1;
-        }
+    __shared__ int slot;
+    typedef const __attribute__((address_space(1))) GroupedDesc* gdesc;
+    const gdesc dg = (gdesc)desc;
+    TileClaims claims(q, counters);
+    for (int tile = claims.first(&slot); tile >= 0; tile = claims.next(&slot)) {
+        claims.prefetch();
+        const int lo = wave_find_last(count, tile, [&](int i) { return dg[i].tile_start; });
         const int tiles_n = dg[lo].tiles_n;
-        const int local = tile - dg[lo].tile_start;
+        const int local = tile - dg[lo].tile_start + dg[lo].tile_first;
         const int tm = local / tiles_n, tn = local - (local / tiles_n) * tiles_n;
         const F32Problem p{dg[lo].M, dg[lo].N, dg[lo].K, dg[lo].lda, dg[lo].ldb, dg[lo].ldc,
                             dg[lo].alpha, dg[lo].beta, dg[lo].A, dg[lo].B, dg[lo].C};
         f32_tile<Cfg>(p, (int64_t)tm * Cfg::BM, (int64_t)tn * Cfg::BN, dg[lo].vec != 0, smem);
-        __syncthreads();  // LDS is reused by the next tile; next_tile read by every lane
-        if (threadIdx.x == 0) {
-            const unsigned ticket = atomicAdd(counter, 1u);
-            const unsigned left = (unsigned)total_tiles - gridDim.x;   // grid <= total_tiles
-            next_tile = ticket < left ? (int)(gridDim.x + ticket) : total_tiles;
-        }
-        __syncthreads();
-        tile = next_tile;
+        // claims.next starts with a barrier: the ring is free for the next tile
     }
+    claims.finish();
 }
 
 __global__ void scale_c_kernel(int64_t M, int64_t N, float beta, float* __restrict__ C,
@@ -87,11 +80,9 @@ __global__ void scale_c_kernel(int64_t M, int64_t N, float beta, float* __restri
 }
 
 template <typename Cfg>
-hipError_t launch_grouped_cfg(const GroupedDesc* desc, int count, int total_tiles, int grid,
-                              unsigned* counter, hipStream_t stream) {
-    hipLaunchKernelGGL(grouped_reset_kernel, dim3(1), dim3(64), 0, stream, counter);
-    hipLaunchKernelGGL(gemm_f32_grouped_kernel<Cfg>, dim3(grid), dim3(256), 0, stream, desc, count,
-                       total_tiles, counter);
+hipError_t launch_grouped_cfg(const GroupedDesc* desc, int count, const TileQueues& q, int grid,
+                              unsigned* counters, hipStream_t stream) {
+    hipLaunchKernelGGL(gemm_f32_grouped_kernel<Cfg>, dim3(grid), dim3(256), 0, stream, desc, count, q, counters);
     return hipGetLastError();
 }
 
@@ -103,21 +94,21 @@ const GroupedConfig kGroupedConfigs[kNumGroupedConfigs] = {
     {64, 64, 64}, {64, 128, 64},
 };
 
-hipError_t launch_gemm_f32_grouped(int config, const GroupedDesc* desc, int count, int total_tiles,
-                                   int grid, unsigned* counter, hipStream_t stream) {
-    if (total_tiles <= 0) return hipSuccess;
-    if (grid < 1 || grid > total_tiles || !counter) return hipErrorInvalidValue;
+hipError_t launch_gemm_f32_grouped(int config, const GroupedDesc* desc, int count, const TileQueues& q,
+                                   int grid, unsigned* counters, hipStream_t stream) {
+    if (q.start[kXcds] <= 0) return hipSuccess;
+    if (grid < 1 || grid > q.start[kXcds] || !counters || count < 1) return hipErrorInvalidValue;
     switch (config) {
-        case 0: return launch_grouped_cfg<F32Cfg<64, 64, 16, 32, 4>>(desc, count, total_tiles, grid, counter, stream);
-        case 1: return launch_grouped_cfg<F32Cfg<64, 64, 32, 32, 3>>(desc, count, total_tiles, grid, counter, stream);
-        case 2: return launch_grouped_cfg<F32Cfg<64, 128, 16, 32, 3>>(desc, count, total_tiles, grid, counter, stream);
-        case 3: return launch_grouped_cfg<F32Cfg<128, 64, 16, 32, 3>>(desc, count, total_tiles, grid, counter, stream);
-        case 4: return launch_grouped_cfg<F32Cfg<128, 128, 16, 32, 3>>(desc, count, total_tiles, grid, counter, stream);
-        case 5: return launch_grouped_cfg<F32Cfg<128, 128, 32, 32, 2>>(desc, count, total_tiles, grid, counter, stream);
-        case 6: return launch_grouped_cfg<F32Cfg<256, 128, 16, 32, 2>>(desc, count, total_tiles, grid, counter, stream);
-        case 7: return launch_grouped_cfg<F32Cfg<128, 256, 16, 32, 2>>(desc, count, total_tiles, grid, counter, stream);
-        case 8: return launch_grouped_cfg<F32Cfg<64, 64, 64, 32, 2>>(desc, count, total_tiles, grid, counter, stream);
-        case 9: return launch_grouped_cfg<F32Cfg<64, 128, 64, 32, 2>>(desc, count, total_tiles, grid, counter, stream);
+        case 0: return launch_grouped_cfg<F32Cfg<64, 64, 16, 32, 4>>(desc, count, q, grid, counters, stream);
+        case 1: return launch_grouped_cfg<F32Cfg<64, 64, 32, 32, 3>>(desc, count, q, grid, counters, stream);
+        case 2: return launch_grouped_cfg<F32Cfg<64, 128, 16, 32, 3>>(desc, count, q, grid, counters, stream);
+        case 3: return launch_grouped_cfg<F32Cfg<128, 64, 16, 32, 3>>(desc, count, q, grid, counters, stream);
+        case 4: return launch_grouped_cfg<F32Cfg<128, 128, 16, 32, 3>>(desc, count, q, grid, counters, stream);
+        case 5: return launch_grouped_cfg<F32Cfg<128, 128, 32, 32, 2>>(desc, count, q, grid, counters, stream);
+        case 6: return launch_grouped_cfg<F32Cfg<256, 128, 16, 32, 2>>(desc, count, q, grid, counters, stream);
+        case 7: return launch_grouped_cfg<F32Cfg<128, 256, 16, 32, 2>>(desc, count, q, grid, counters, stream);
+        case 8: return launch_grouped_cfg<F32Cfg<64, 64, 64, 32, 2>>(desc, count, q, grid, counters, stream);
+        case 9: return launch_grouped_cfg<F32Cfg<64, 128, 64, 32, 2>>(desc, count, q, grid, counters, stream);
         default: return hipErrorInvalidValue;
     }
 }

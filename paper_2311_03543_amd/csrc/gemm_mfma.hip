@@ -457,46 +457,31 @@ void gemm_bf16x3_slab4_kernel(int64_t M, int64_t N, int nkb, float alpha,
 }
 
 // Many bf16x3 problems in one persistent launch (the grouped plan's MFMA
-// configuration): the tile list is the concatenation of every problem's
-// 256 x 256 tiles (desc[p].tile_start = first tile of problem p, problems in
-// decreasing order of K).  Workgroup b starts with tile b and each workgroup
-// that finishes a tile claims the next unclaimed one from `counter` (zeroed
-// by grouped_mfma_reset_kernel right before, on the same stream).  The tile
-// index lives in the 16 bytes past the ring, so the LDS request is kSmem + 16.
-__global__ void grouped_mfma_reset_kernel(unsigned* counter) {
-    if (threadIdx.x == 0) *counter = 0u;
-}
-
+// configuration) over the tile lists of `q` (common.h): each workgroup works
+// through 256 x 256 tiles, claiming the next one while it computes.  The
+// claimed tile passes through the 16 bytes past the ring, so the LDS request
+// is kSmem + 16.
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void gemm_bf16x3_grouped_kernel(const GroupedMfmaDesc* __restrict__ desc, int count, int total_tiles,
-                                unsigned* __restrict__ counter) {
+void gemm_bf16x3_grouped_kernel(const GroupedMfmaDesc* __restrict__ desc, int count, TileQueues q,
+                                unsigned* __restrict__ counters) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    int* next_tile = reinterpret_cast<int*>(smem + kSmem);
+    int* slot = reinterpret_cast<int*>(smem + kSmem);
     typedef const __attribute__((address_space(1))) GroupedMfmaDesc* gdesc;
     const gdesc dg = (gdesc)desc;
-    for (int tile = blockIdx.x; tile < total_tiles;) {
-        int lo = 0, hi = count - 1;            // last problem whose first tile is <= tile
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (dg[mid].tile_start <= tile) lo = mid;
-            else hi = mid - 1;
-        }
-        const int local = tile - dg[lo].tile_start;
+    TileClaims claims(q, counters);
+    for (int tile = claims.first(slot); tile >= 0; tile = claims.next(slot)) {
+        claims.prefetch();
+        const int lo = wave_find_last(count, tile, [&](int i) { return dg[i].tile_start; });
+        const int local = tile - dg[lo].tile_start + dg[lo].tile_first;
         const int tn_count = dg[lo].tiles_n;
         const int tm = local / tn_count, tn = local - tm * tn_count;
         const int nkb = (int)(dg[lo].Kp * 2 / kPanelRowBytes);
         bf16x3_tile(smem, dg[lo].M, dg[lo].N, nkb, dg[lo].alpha, (const uint8_t*)dg[lo].ah,
                     (const uint8_t*)dg[lo].al, (const uint8_t*)dg[lo].bh, (const uint8_t*)dg[lo].bl,
                     dg[lo].beta, dg[lo].C, dg[lo].ldc, tm, tn, 0, nkb, nullptr);
-        __syncthreads();                       // every wave is done with the ring and next_tile
-        if (threadIdx.x == 0) {
-            const unsigned ticket = atomicAdd(counter, 1u);
-            const unsigned left = (unsigned)total_tiles - gridDim.x;   // grid <= total_tiles
-            *next_tile = ticket < left ? (int)(gridDim.x + ticket) : total_tiles;
-        }
-        __syncthreads();
-        tile = __builtin_amdgcn_readfirstlane(*next_tile);
+        // claims.next starts with a barrier: the ring is free for the next tile
     }
+    claims.finish();
 }
 
 // ---------------------------------------------------------------------------
@@ -985,15 +970,14 @@ hipError_t launch_gemm_bf16_tn(int64_t M, int64_t N, int64_t Kp, int nterms, flo
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_bf16x3_grouped(const GroupedMfmaDesc* desc, int count, int total_tiles, int grid,
-                                      unsigned* counter, hipStream_t stream) {
-    if (total_tiles <= 0) return hipSuccess;
-    if (grid < 1 || grid > total_tiles || !counter || !desc || count < 1) return hipErrorInvalidValue;
+hipError_t launch_gemm_bf16x3_grouped(const GroupedMfmaDesc* desc, int count, const TileQueues& q, int grid,
+                                      unsigned* counters, hipStream_t stream) {
+    if (q.start[kXcds] <= 0) return hipSuccess;
+    if (grid < 1 || grid > q.start[kXcds] || !counters || !desc || count < 1) return hipErrorInvalidValue;
     static std::atomic<uint64_t> lds_g{0};
     if (hipError_t e = allow_lds(gemm_bf16x3_grouped_kernel, lds_g, kSmem + 16)) return e;
-    hipLaunchKernelGGL(grouped_mfma_reset_kernel, dim3(1), dim3(64), 0, stream, counter);
-    hipLaunchKernelGGL(gemm_bf16x3_grouped_kernel, dim3(grid), dim3(THREADS), kSmem + 16, stream, desc, count,
-                       total_tiles, counter);
+    hipLaunchKernelGGL(gemm_bf16x3_grouped_kernel, dim3(grid), dim3(THREADS), kSmem + 16, stream, desc, count, q,
+                       counters);
     return hipGetLastError();
 }
 

@@ -7,6 +7,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "common.h"
+
 namespace cmp {
 
 // ---- FP32 GEMM on the host CPU (host_gemm.cpp) ------------------------------
@@ -20,27 +22,28 @@ hipError_t launch_gemm_f32_simt(int64_t M, int64_t N, int64_t K, float alpha,
                                 const float* A, int64_t lda, const float* B, int64_t ldb,
                                 float beta, float* C, int64_t ldc, hipStream_t stream);
 
-// Grouped FP32 launch over many problems of uneven shapes.  The
-// descriptor array (device memory) lists the problems in launch order with
-// the first tile index of each (prefix sum of tiles_m * tiles_n); `grid`
-// persistent workgroups stride over all `total_tiles`.  `vec` marks problems
-// whose A and B allow 16-byte loads (lda, ldb multiples of 4, 16-byte aligned).
+// Grouped FP32 launch over many problems of uneven shapes.  The descriptor
+// array (device memory) lists pieces of problems, all their tiles or a run of
+// them from tile `tile_first` on, in the order of the tile lists (common.h,
+// TileQueues); tile_start is a piece's first place in the list.  `vec` marks
+// problems whose A and B allow 16-byte loads (lda, ldb multiples of 4, 16-byte
+// aligned).
 struct GroupedDesc {
     int64_t M, N, K, lda, ldb, ldc;
     float alpha, beta;
     const float* A;
     const float* B;
     float* C;
-    int tiles_n, tile_start, vec, pad;
+    int tiles_n, tile_start, vec, tile_first;
 };
 struct GroupedConfig {
     int bm, bn, bk;
 };
 // One problem of a grouped bf16x3 launch: the operands, the problem's
 // bf16 hi / lo panel images (Mp x Kp of A, Np x Kp of B^T, in the plan's
-// workspace), the pre-pass workgroups of A (ga) and B (gb) from pre_start on,
-// and the problem's 256 x 256 tiles from tile_start on.  vec: bit 0 A, bit 1 B
-// can be read with 16-byte loads.
+// workspace), the pre-pass workgroups of A (ga) and B (gb) from pre_start on
+// (none in a problem's further pieces), and the piece's 256 x 256 tiles, as in
+// GroupedDesc.  vec: bit 0 A, bit 1 B can be read with 16-byte loads.
 struct GroupedMfmaDesc {
     int64_t M, N, K, lda, ldb, ldc, Mp, Np, Kp;
     float alpha, beta;
@@ -48,22 +51,22 @@ struct GroupedMfmaDesc {
     const float* B;
     float* C;
     uint16_t *ah, *al, *bh, *bl;
-    int ga, gb, pre_start, tile_start, tiles_n, vec;
+    int ga, gb, pre_start, tile_start, tiles_n, vec, tile_first;
 };
 constexpr int kNumGroupedConfigs = 10;
 extern const GroupedConfig kGroupedConfigs[kNumGroupedConfigs];
-// One persistent launch over the problems of `desc` (tile list in desc order,
-// 1 <= grid <= total_tiles workgroups), preceded by a one-lane kernel that
-// zeroes `counter` (device, 4 bytes), the tile queue the workgroups claim from;
-// launches of one counter must not overlap.
+// One persistent launch over the pieces of `desc` and the tile lists `q`
+// (1 <= grid <= q.start[8] workgroups).  `counters`: device, kQueueWords words
+// the workgroups claim from, zero before the first launch and left zero by
+// each; launches of the same counters must not overlap.
+hipError_t launch_gemm_f32_grouped(int config, const GroupedDesc* desc, int count, const TileQueues& q,
+                                   int grid, unsigned* counters, hipStream_t stream);
 // Grouped bf16x3: the hi / lo images of every problem in one launch (pre_total
 // workgroups), then every problem's tiles in one persistent launch.
 hipError_t launch_split_grouped(const GroupedMfmaDesc* desc, int count, int64_t pre_total,
                                 hipStream_t stream);
-hipError_t launch_gemm_bf16x3_grouped(const GroupedMfmaDesc* desc, int count, int total_tiles, int grid,
-                                      unsigned* counter, hipStream_t stream);
-hipError_t launch_gemm_f32_grouped(int config, const GroupedDesc* desc, int count, int total_tiles,
-                                   int grid, unsigned* counter, hipStream_t stream);
+hipError_t launch_gemm_bf16x3_grouped(const GroupedMfmaDesc* desc, int count, const TileQueues& q, int grid,
+                                      unsigned* counters, hipStream_t stream);
 // Resident workgroups per CU of the grouped kernel for a configuration.
 int grouped_blocks_per_cu(int config);
 

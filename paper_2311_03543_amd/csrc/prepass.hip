@@ -167,8 +167,8 @@ __global__ __launch_bounds__(256) void split_pair_kernel(SplitPair p) {
 }
 
 // The hi / lo images of every problem of a grouped bf16x3 plan in one launch:
-// workgroup w belongs to the problem p with desc[p].pre_start <= w (problems
-// in list order, each A's ga workgroups then B's gb), one split_a chunk pass
+// workgroup w belongs to the last piece p with desc[p].pre_start <= w (each
+// problem's A workgroups, ga, then B's, gb), one split_a chunk pass
 // or one split_bt tile per workgroup.  Only rows below M (A, whose idle
 // 64-row quarters get no workgroup) and the 64-row tiles that start below N
 // (B^T) are written: padding rows of an image feed
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256) void split_grouped_kernel(const GroupedMfmaDes
     typedef const __attribute__((address_space(1))) GroupedMfmaDesc* gdesc;
     const gdesc dg = (gdesc)desc;
     const int w = (int)blockIdx.x;
-    int lo = 0, hi = count - 1;
+    int lo = 0, hi = count - 1;               // scalar loads that neighbouring workgroups share
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (dg[mid].pre_start <= w) lo = mid;

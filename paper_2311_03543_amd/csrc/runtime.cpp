@@ -2382,13 +2382,14 @@ struct cmp_grouped_plan {
     cmp_ctx* ctx = nullptr;
     int count = 0;           // problems with at least one tile
     int config = -1;
-    int total_tiles = 0;
+    int pieces = 0;          // descriptors (a problem's tiles may be cut into several)
+    cmp::TileQueues queues{};
     int grid = 0;
-    cmp::GroupedDesc* desc = nullptr;     // device: the descriptors, then the tile-queue counter
+    cmp::GroupedDesc* desc = nullptr;     // device: the descriptors, then the tile-list counters
     cmp::GroupedMfmaDesc* mdesc = nullptr;   // the same for the bf16x3 configuration
     void* images = nullptr;               // device: that configuration's bf16 hi / lo images
     int64_t pre_total = 0;                // its pre-pass workgroups
-    unsigned* counter = nullptr;          // device, inside the descriptor allocation
+    unsigned* counters = nullptr;         // device, inside the descriptor allocation: one per tile list
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<float> config_ms;         // autotuner medians per configuration (NaN: not tried)
@@ -2396,53 +2397,105 @@ struct cmp_grouped_plan {
 
 namespace {
 
-// Descriptors for one tile configuration.  A tile's time grows with its
-// problem's K, so problems go in decreasing order of K (then of M x N): the
-// kernel hands tiles out greedily in list order, and serving the longest
-// tiles first keeps the finishing times of the workgroups close together.
-int build_descs(cmp_ctx* c, const std::vector<cmp_gemm_args>& probs, int config,
-                std::vector<cmp::GroupedDesc>* out, int* total) {
-    const int bm = cmp::kGroupedConfigs[config].bm, bn = cmp::kGroupedConfigs[config].bn;
-    std::vector<int> order;
-    for (int i = 0; i < (int)probs.size(); ++i)
-        if (probs[i].M > 0 && probs[i].N > 0) order.push_back(i);
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-        if (probs[x].K != probs[y].K) return probs[x].K > probs[y].K;
-        return (double)probs[x].M * probs[x].N > (double)probs[y].M * probs[y].N;
-    });
+// The tile lists of a group for one tile shape.  Whole problems go to the
+// eight lists, largest work first to the list with the least, so that one XCD's
+// L2 serves all tiles of a problem; problems above 1/32 of the total are cut
+// into pieces first, which keeps the lists even when a few problems hold most
+// of the work.  A tile's time grows with its problem's K, so each list holds its
+// pieces in decreasing order of K (then of M x N): the kernel serves a list in
+// order, and the longest tiles first keeps the finishing times close together.
+// (512 problems in [32, 1024] as one list shared by all XCDs read 1.1 GB where
+// 0.51 are needed.)
+struct Piece {
+    int problem, first, tiles;
+};
+int tile_lists(cmp_ctx* c, const std::vector<cmp_gemm_args>& probs, int bm, int bn, std::vector<Piece>* out,
+               cmp::TileQueues* q, int* problems) {
+    const auto tiles_of = [&](const cmp_gemm_args& a) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
+    const auto tile_work = [&](const cmp_gemm_args& a) { return (double)(a.alpha == 0.f ? 0 : a.K) + 64.0; };
+    int64_t total = 0;
+    double work = 0;
+    *problems = 0;
+    for (const auto& a : probs) {
+        if (a.M <= 0 || a.N <= 0) continue;
+        total += tiles_of(a);
+        work += (double)tiles_of(a) * tile_work(a);
+        ++*problems;
+        if (total > INT32_MAX) return fail(c, CMP_EINVAL, "grouped launch exceeds 2^31 tiles");
+    }
+    std::vector<Piece> pieces;
+    for (int i = 0; i < (int)probs.size(); ++i) {
+        if (probs[i].M <= 0 || probs[i].N <= 0) continue;
+        const int64_t n = tiles_of(probs[i]);
+        const int64_t most = std::max<int64_t>(1, (int64_t)(work / 32 / tile_work(probs[i])));
+        const int64_t cuts = (n + most - 1) / most;
+        for (int64_t k = 0; k < cuts; ++k)
+            pieces.push_back({i, (int)(n * k / cuts), (int)(n * (k + 1) / cuts - n * k / cuts)});
+    }
+    const auto piece_work = [&](const Piece& p) { return (double)p.tiles * tile_work(probs[p.problem]); };
+    std::stable_sort(pieces.begin(), pieces.end(),
+                     [&](const Piece& x, const Piece& y) { return piece_work(x) > piece_work(y); });
+    std::vector<Piece> list[cmp::kXcds];
+    double load[cmp::kXcds] = {};
+    for (const Piece& p : pieces) {
+        const int x = (int)(std::min_element(load, load + cmp::kXcds) - load);
+        list[x].push_back(p);
+        load[x] += piece_work(p);
+    }
     out->clear();
     int64_t start = 0;
-    for (int i : order) {
-        const cmp_gemm_args& a = probs[i];
+    for (int x = 0; x < cmp::kXcds; ++x) {
+        std::stable_sort(list[x].begin(), list[x].end(), [&](const Piece& p, const Piece& r) {
+            const auto &a = probs[p.problem], &b = probs[r.problem];
+            if (a.K != b.K) return a.K > b.K;
+            return (double)a.M * a.N > (double)b.M * b.N;
+        });
+        q->start[x] = (int)start;
+        for (const Piece& p : list[x]) {
+            out->push_back(p);
+            start += p.tiles;
+        }
+    }
+    q->start[cmp::kXcds] = (int)start;
+    return CMP_OK;
+}
+
+// Descriptors for one FP32 tile configuration, in list order.
+int build_descs(cmp_ctx* c, const std::vector<cmp_gemm_args>& probs, int config, cmp_grouped_plan* pl,
+                std::vector<cmp::GroupedDesc>* out) {
+    const int bm = cmp::kGroupedConfigs[config].bm, bn = cmp::kGroupedConfigs[config].bn;
+    std::vector<Piece> pieces;
+    if (int st = tile_lists(c, probs, bm, bn, &pieces, &pl->queues, &pl->count)) return st;
+    out->clear();
+    int start = 0;
+    for (const Piece& p : pieces) {
+        const cmp_gemm_args& a = probs[p.problem];
         cmp::GroupedDesc d{};
         d.M = a.M; d.N = a.N; d.K = a.K;
         d.lda = a.lda; d.ldb = a.ldb; d.ldc = a.ldc;
         d.alpha = a.alpha; d.beta = a.beta;
         d.A = a.A; d.B = a.B; d.C = a.C;
-        const int64_t tm = (a.M + bm - 1) / bm, tn = (a.N + bn - 1) / bn;
-        d.tiles_n = (int)tn;
-        d.tile_start = (int)start;
+        d.tiles_n = (int)((a.N + bn - 1) / bn);
+        d.tile_start = start;
+        d.tile_first = p.first;
         d.vec = (a.lda % 4 == 0) && (a.ldb % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.A) & 15) == 0) &&
                 ((reinterpret_cast<uintptr_t>(a.B) & 15) == 0);
-        start += tm * tn;
-        if (start > INT32_MAX) return fail(c, CMP_EINVAL, "grouped launch exceeds 2^31 tiles");
+        start += p.tiles;
         out->push_back(d);
     }
-    *total = (int)start;
+    pl->pieces = (int)out->size();
     return CMP_OK;
 }
 
-int upload_descs(cmp_ctx* c, cmp_grouped_plan* pl, const std::vector<cmp::GroupedDesc>& d,
-                 hipStream_t s) {
-    if (pl->desc) HIP_TRY(c, hipFree(pl->desc));
-    pl->desc = nullptr;
-    pl->counter = nullptr;
-    const size_t dbytes = (size_t)round_up((int64_t)(std::max<size_t>(d.size(), 1) * sizeof(cmp::GroupedDesc)), 256);
-    HIP_TRY(c, hipMalloc(&pl->desc, dbytes + 256));
-    pl->counter = reinterpret_cast<unsigned*>(reinterpret_cast<uint8_t*>(pl->desc) + dbytes);
-    if (!d.empty())
-        HIP_TRY(c, hipMemcpyAsync(pl->desc, d.data(), d.size() * sizeof(cmp::GroupedDesc),
-                                  hipMemcpyHostToDevice, s));
+// Device copies of the descriptors, followed by the tile-list counters.
+template <class Desc>
+int upload_descs(cmp_ctx* c, cmp_grouped_plan* pl, const std::vector<Desc>& d, Desc** dst, hipStream_t s) {
+    const size_t dbytes = (size_t)round_up((int64_t)(std::max<size_t>(d.size(), 1) * sizeof(Desc)), 256);
+    std::vector<uint8_t> image(dbytes + cmp::kQueueWords * sizeof(unsigned), 0);   // the counters start at zero
+    if (!d.empty()) std::memcpy(image.data(), d.data(), d.size() * sizeof(Desc));
+    HIP_TRY(c, hipMalloc(dst, image.size()));
+    pl->counters = reinterpret_cast<unsigned*>(reinterpret_cast<uint8_t*>(*dst) + dbytes);
+    HIP_TRY(c, hipMemcpyAsync(*dst, image.data(), image.size(), hipMemcpyHostToDevice, s));
     HIP_TRY(c, hipStreamSynchronize(s));
     return CMP_OK;
 }
@@ -2473,26 +2526,22 @@ void free_plan_buffers(cmp_grouped_plan* pl) {
     pl->desc = nullptr;
     pl->mdesc = nullptr;
     pl->images = nullptr;
-    pl->counter = nullptr;
+    pl->counters = nullptr;
     pl->pre_total = 0;
 }
 
-// Descriptors, images and counter of the bf16x3 configuration (problem order
-// as in build_descs).
+// Descriptors, images and counters of the bf16x3 configuration.
 int build_mfma(cmp_ctx* c, cmp_grouped_plan* pl, const std::vector<cmp_gemm_args>& probs, hipStream_t s) {
-    std::vector<int> order;
-    for (int i = 0; i < (int)probs.size(); ++i)
-        if (probs[i].M > 0 && probs[i].N > 0) order.push_back(i);
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-        if (probs[x].K != probs[y].K) return probs[x].K > probs[y].K;
-        return (double)probs[x].M * probs[x].N > (double)probs[y].M * probs[y].N;
-    });
+    std::vector<Piece> pieces;
+    if (int st = tile_lists(c, probs, cmp::kMfmaTileM, cmp::kMfmaTileN, &pieces, &pl->queues, &pl->count)) return st;
     std::vector<cmp::GroupedMfmaDesc> d;
-    std::vector<size_t> img_off;              // per problem: offset of its four images
+    std::vector<size_t> img_off;              // per piece: offset of its problem's four images
+    std::vector<int64_t> placed(probs.size(), -1);
     size_t img_bytes = 0;
-    int64_t pre = 0, tiles = 0;
-    for (int i : order) {
-        const cmp_gemm_args& a = probs[i];
+    int64_t pre = 0;
+    int tiles = 0;
+    for (const Piece& p : pieces) {
+        const cmp_gemm_args& a = probs[p.problem];
         cmp::GroupedMfmaDesc g{};
         g.M = a.M; g.N = a.N; g.K = a.K;
         g.lda = a.lda; g.ldb = a.ldb; g.ldc = a.ldc;
@@ -2501,21 +2550,27 @@ int build_mfma(cmp_ctx* c, cmp_grouped_plan* pl, const std::vector<cmp_gemm_args
         g.Kp = round_up(a.K, cmp::kBf16TileK);
         g.alpha = a.alpha; g.beta = a.beta;
         g.A = a.A; g.B = a.B; g.C = a.C;
-        // A: one workgroup per 64-row quarter of a 256-row x 64-byte block below M
-        g.ga = (int)((a.M / 256 * 4 + (a.M % 256 + 63) / 64) * (g.Kp * 2 / 64));
-        g.gb = (int)(((a.N + 63) / 64) * (g.Kp / 64));   // the 64-row tiles of B^T below N
         g.pre_start = (int)pre;
-        g.tile_start = (int)tiles;
+        g.tile_start = tiles;
+        g.tile_first = p.first;
         g.tiles_n = (int)(g.Np / cmp::kMfmaTileN);
         g.vec = ((a.lda % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.A) & 15) == 0) ? 1 : 0) |
                 ((a.ldb % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.B) & 15) == 0) ? 2 : 0);
-        pre += (int64_t)g.ga + g.gb;
-        tiles += (g.Mp / cmp::kMfmaTileM) * (g.Np / cmp::kMfmaTileN);
-        // (a workgroup's copy offsets reach its panel's K blocks: 64 bytes of K x 256 rows each)
-        if (pre > INT32_MAX || tiles > INT32_MAX || g.Kp * 2 / 64 * 16384 > INT32_MAX)
-            return fail(c, CMP_EINVAL, "grouped bf16x3 launch too large");
-        img_off.push_back(img_bytes);
-        img_bytes += (size_t)round_up(g.Mp * g.Kp * 2, 256) * 2 + (size_t)round_up(g.Np * g.Kp * 2, 256) * 2;
+        if (placed[p.problem] < 0) {          // the problem's first piece brings its pre-pass
+            // A: one workgroup per 64-row quarter of a 256-row x 64-byte block below M
+            const int64_t ga = (a.M / 256 * 4 + (a.M % 256 + 63) / 64) * (g.Kp * 2 / 64);
+            const int64_t gb = ((a.N + 63) / 64) * (g.Kp / 64);   // the 64-row tiles of B^T below N
+            pre += ga + gb;
+            // (a workgroup's copy offsets reach its panel's K blocks: 64 bytes of K x 256 rows each)
+            if (pre > INT32_MAX || g.Kp * 2 / 64 * 16384 > INT32_MAX)
+                return fail(c, CMP_EINVAL, "grouped bf16x3 launch too large");
+            g.ga = (int)ga;
+            g.gb = (int)gb;
+            placed[p.problem] = (int64_t)img_bytes;
+            img_bytes += (size_t)round_up(g.Mp * g.Kp * 2, 256) * 2 + (size_t)round_up(g.Np * g.Kp * 2, 256) * 2;
+        }
+        tiles += p.tiles;
+        img_off.push_back((size_t)placed[p.problem]);
         d.push_back(g);
     }
     if (img_bytes) HIP_TRY(c, hipMalloc(&pl->images, img_bytes));
@@ -2527,17 +2582,10 @@ int build_mfma(cmp_ctx* c, cmp_grouped_plan* pl, const std::vector<cmp_gemm_args
         d[p].bh = reinterpret_cast<uint16_t*>(base + 2 * as);
         d[p].bl = reinterpret_cast<uint16_t*>(base + 2 * as + bs);
     }
-    const size_t dbytes = (size_t)round_up((int64_t)(std::max<size_t>(d.size(), 1) * sizeof(cmp::GroupedMfmaDesc)), 256);
-    HIP_TRY(c, hipMalloc(&pl->mdesc, dbytes + 256));
-    pl->counter = reinterpret_cast<unsigned*>(reinterpret_cast<uint8_t*>(pl->mdesc) + dbytes);
-    if (!d.empty())
-        HIP_TRY(c, hipMemcpyAsync(pl->mdesc, d.data(), d.size() * sizeof(cmp::GroupedMfmaDesc),
-                                  hipMemcpyHostToDevice, s));
-    HIP_TRY(c, hipStreamSynchronize(s));
-    pl->count = (int)d.size();
-    pl->total_tiles = (int)tiles;
+    if (int st = upload_descs(c, pl, d, &pl->mdesc, s)) return st;
+    pl->pieces = (int)d.size();
     pl->pre_total = pre;
-    pl->grid = std::max(1, std::min((int)tiles, c->props.multiProcessorCount));   // one 128 KiB ring per CU
+    pl->grid = std::max(1, std::min(tiles, c->props.multiProcessorCount));   // one 128 KiB ring per CU
     return CMP_OK;
 }
 
@@ -2548,24 +2596,21 @@ int setup_config(cmp_ctx* c, cmp_grouped_plan* pl, const std::vector<cmp_gemm_ar
     pl->config = cfg;
     if (cfg == kGroupedMfma) return build_mfma(c, pl, probs, s);
     std::vector<cmp::GroupedDesc> d;
-    int total = 0, st;
-    if ((st = build_descs(c, probs, cfg, &d, &total))) return st;
-    if ((st = upload_descs(c, pl, d, s))) return st;
-    pl->count = (int)d.size();
-    pl->total_tiles = total;
-    pl->grid = grouped_grid(c, cfg, total);
+    int st;
+    if ((st = build_descs(c, probs, cfg, pl, &d))) return st;
+    if ((st = upload_descs(c, pl, d, &pl->desc, s))) return st;
+    pl->grid = grouped_grid(c, cfg, pl->queues.start[cmp::kXcds]);
     return CMP_OK;
 }
 
 hipError_t plan_launch(cmp_grouped_plan* pl, hipStream_t s) {
     if (pl->config == kGroupedMfma) {
-        hipError_t e = cmp::launch_split_grouped(pl->mdesc, pl->count, pl->pre_total, s);
+        hipError_t e = cmp::launch_split_grouped(pl->mdesc, pl->pieces, pl->pre_total, s);
         if (e == hipSuccess)
-            e = cmp::launch_gemm_bf16x3_grouped(pl->mdesc, pl->count, pl->total_tiles, pl->grid, pl->counter, s);
+            e = cmp::launch_gemm_bf16x3_grouped(pl->mdesc, pl->pieces, pl->queues, pl->grid, pl->counters, s);
         return e;
     }
-    return cmp::launch_gemm_f32_grouped(pl->config, pl->desc, pl->count, pl->total_tiles, pl->grid,
-                                        pl->counter, s);
+    return cmp::launch_gemm_f32_grouped(pl->config, pl->desc, pl->pieces, pl->queues, pl->grid, pl->counters, s);
 }
 
 }  // namespace
@@ -2685,7 +2730,7 @@ CMP_API int cmp_grouped_plan_info(const cmp_grouped_plan* pl, int* config, int* 
     if (!pl) return CMP_EINVAL;
     if (config) *config = pl->config;
     if (problems) *problems = pl->count;
-    if (tiles) *tiles = pl->total_tiles;
+    if (tiles) *tiles = pl->queues.start[cmp::kXcds];
     if (grid) *grid = pl->grid;
     if (config_ms)
         for (int i = 0; i < kGroupedAll; ++i) config_ms[i] = pl->config_ms[i];
