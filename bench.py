@@ -51,9 +51,9 @@ def kernel_roofline(name: str, M: int, N: int, K: int):
     Kp128 = -(-K // 128) * 128
     if name == "gemm_f32_simt":
         return "alu", 2.0 * M * N * K, PEAK["fp32_vector"], "TFLOP/s"
-    if name == "gemm_bf16_tn":
+    if name in ("gemm_bf16_tn", "gemm_bf16_direct"):
         return "mfma", 2.0 * M * N * K, PEAK["bf16"], "TFLOP/s"
-    if name == "gemm_bf16x3_tn":
+    if name in ("gemm_bf16x3_tn", "gemm_bf16x3_direct"):
         return "mfma", 3 * 2.0 * M * N * K, PEAK["bf16"], "TFLOP/s"
     if name == "gemm_fp8r_tn":
         return "mfma", 4 * 2.0 * M * N * K, PEAK["fp8"], "TFLOP/s"
@@ -76,6 +76,8 @@ KERNEL_SOURCES = {  # kernel name -> source file (relative to the repo root)
     "gemm_f32_simt": "paper_2311_03543_amd/csrc/gemm_f32_simt.hip",
     "gemm_bf16_tn": "paper_2311_03543_amd/csrc/gemm_mfma.hip",
     "gemm_bf16x3_tn": "paper_2311_03543_amd/csrc/gemm_mfma.hip",
+    "gemm_bf16_direct": "paper_2311_03543_amd/csrc/gemm_direct.hip",
+    "gemm_bf16x3_direct": "paper_2311_03543_amd/csrc/gemm_direct.hip",
     "gemm_fp8r_tn": "paper_2311_03543_amd/csrc/gemm_mfma.hip",
     "gemm_fp6x3_tn": "paper_2311_03543_amd/csrc/gemm_mfma.hip",
 }

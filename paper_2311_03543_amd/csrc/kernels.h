@@ -144,6 +144,20 @@ hipError_t launch_gemm_bf16_tn(int64_t M, int64_t N, int64_t Kp, int nterms, flo
                                const uint16_t* Bh, const uint16_t* Bl,
                                float beta, float* C, int64_t ldc, int splits, float* partial,
                                hipStream_t stream);
+// The same product straight from the FP32 operands, without images
+// (gemm_direct.hip), where that is expected to be faster: tile 0 = use the
+// images; otherwise the tile (128, or 127: 128 with one group over K; 64, or 63:
+// 64 with more groups over K) and the K slices (> 1: slice s writes its raw sum to partial + s * M * N, as
+// above).  image_splits: the slices the image form would take; ws_bytes: room
+// for partial sums.
+struct DirectPlan {
+    int tile = 0, slices = 1;
+};
+DirectPlan direct_plan(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int nterms, int image_splits,
+                       size_t ws_bytes);
+hipError_t launch_gemm_bf16_direct(const DirectPlan& plan, int64_t M, int64_t N, int64_t K, int nterms, float alpha,
+                                   const float* A, int64_t lda, const float* B, int64_t ldb, float beta, float* C,
+                                   int64_t ldc, float* partial, hipStream_t stream);
 // fp8 with refinement: C = alpha * (Aq.Bq + Ar.Bq + Aq.Br + Ar.Br) + beta * C,
 // each operand dequantised by its 128 x 128 tile's E8M0 scale byte; splits and
 // partial as above (K slices of 64-byte blocks, splits <= Kp / 64).

@@ -515,6 +515,17 @@ size_t ws_bf16x3(const void* args, void* user) { return ws_images(kImgBf16x3, ar
 size_t ws_fp8r(const void* args, void* user) { return ws_images(kImgFp8r, args, user); }
 size_t ws_fp6x3(const void* args, void* user) { return ws_images(kImgFp6x3, args, user); }
 
+// Whether C's address range meets A's or B's.
+bool output_overlaps(const cmp_gemm_args* a) {
+    const auto meets = [](const float* x, int64_t rows, int64_t cols, int64_t ld, const float* y, int64_t yrows,
+                          int64_t ycols, int64_t yld) {
+        const auto x0 = (uintptr_t)x, y0 = (uintptr_t)y;
+        return x0 < y0 + ((yrows - 1) * yld + ycols) * sizeof(float) && y0 < x0 + ((rows - 1) * ld + cols) * sizeof(float);
+    };
+    return meets(a->C, a->M, a->N, a->ldc, a->A, a->M, a->K, a->lda) ||
+           meets(a->C, a->M, a->N, a->ldc, a->B, a->K, a->N, a->ldb);
+}
+
 // Degenerate shapes shared by every built-in: nothing to do, or C = beta * C.
 bool gemm_trivial(const cmp_gemm_args* a, hipStream_t s, int* st) {
     if (a->M == 0 || a->N == 0) {
@@ -595,6 +606,23 @@ int run_images(cmp_ctx* c, int kind, const cmp_gemm_args* a, void* ws, hipStream
     const Images I = images_of(kind, a->M, a->N, a->K);
     const int splits = image_splits(kind, a, I, c);
     auto* partial = (float*)((uint8_t*)ws + I.total);
+    if ((kind == kImgBf16 || kind == kImgBf16x3) && c->split_k == 0 && !output_overlaps(a)) {
+        // shapes whose images would cost more than they save (a forced slice
+        // count asks for the image kernels, and only those have read an operand
+        // before they write C over it)
+        const int nterms = kind == kImgBf16x3 ? 3 : 1;
+        const cmp::DirectPlan d = cmp::direct_plan(a->M, a->N, a->K, a->lda, a->ldb, nterms, splits,
+                                                   I.total + partial_bytes(a, splits));
+        if (d.tile) {
+            {
+                KTimer kt(c, s, nterms == 3 ? "gemm_bf16x3_direct" : "gemm_bf16_direct");
+                if (cmp::launch_gemm_bf16_direct(d, a->M, a->N, a->K, nterms, a->alpha, a->A, a->lda, a->B, a->ldb,
+                                                 a->beta, a->C, a->ldc, (float*)ws, s) != hipSuccess)
+                    return CMP_EHIP;
+            }
+            return finish_split(c, a, d.slices, (const float*)ws, s);
+        }
+    }
     if ((st = prepass(c, kind, a, I, ws, s))) return st;
     hipError_t e;
     if (kind == kImgBf16 || kind == kImgBf16x3) {
