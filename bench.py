@@ -55,7 +55,7 @@ def kernel_roofline(name: str, M: int, N: int, K: int):
         return "mfma", 2.0 * M * N * K, PEAK["bf16"], "TFLOP/s"
     if name in ("gemm_bf16x3_tn", "gemm_bf16x3_direct"):
         return "mfma", 3 * 2.0 * M * N * K, PEAK["bf16"], "TFLOP/s"
-    if name == "gemm_fp8r_tn":
+    if name in ("gemm_fp8r_tn", "gemm_fp8r_tiles"):
         return "mfma", 4 * 2.0 * M * N * K, PEAK["fp8"], "TFLOP/s"
     if name == "gemm_fp6x3_tn":
         return "mfma", 3 * 2.0 * M * N * K, PEAK["fp6"], "TFLOP/s"
@@ -79,6 +79,7 @@ KERNEL_SOURCES = {  # kernel name -> source file (relative to the repo root)
     "gemm_bf16_direct": "paper_2311_03543_amd/csrc/gemm_direct.hip",
     "gemm_bf16x3_direct": "paper_2311_03543_amd/csrc/gemm_direct.hip",
     "gemm_fp8r_tn": "paper_2311_03543_amd/csrc/gemm_mfma.hip",
+    "gemm_fp8r_tiles": "paper_2311_03543_amd/csrc/gemm_fp8r_tiles.hip",
     "gemm_fp6x3_tn": "paper_2311_03543_amd/csrc/gemm_mfma.hip",
 }
 

@@ -19,8 +19,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcompar.so")
 LIB_SAN = os.path.join(HERE, "libcompar_san.so")
-SOURCES = ["runtime.cpp", "gemm_f32_simt.hip", "gemm_mfma.hip", "gemm_direct.hip", "prepass.hip", "mx6.hip", "freivalds.hip",
-           "mlp.hip", "host_gemm.cpp"]
+SOURCES = ["runtime.cpp", "gemm_f32_simt.hip", "gemm_mfma.hip", "gemm_direct.hip", "gemm_fp8r_tiles.hip",
+           "prepass.hip", "mx6.hip", "freivalds.hip", "mlp.hip", "host_gemm.cpp"]
 ARCH = "gfx950"
 
 

@@ -24,12 +24,12 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "mfma_tile.h"
 
 namespace cmp {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef f32x4 f32x4_word __attribute__((aligned(4)));   // 16-byte load at 4-byte alignment
 typedef const __attribute__((address_space(1))) char* gcbyte;
@@ -57,13 +57,11 @@ struct DirectCfg {
     static constexpr int STAGE = NL * (SLAB_A + SLAB_B);
     static constexpr int U = PF % 2 ? 2 * PF : PF;               // stages per unrolled pass: register sets and LDS halves
     static_assert(BM % 64 == 0 && BN % 64 == 0 && (NT == 1 || NT == 3), "tile");
-    static_assert(KG >= 1 && KG <= 4 && MI * NJ * 16 % KG == 0, "each group finishes its share of the accumulators");
+    static_assert(KG == 1 || KG == 2 || KG == 4, "each group finishes its share of the accumulators");
     // LDS: each group's two stages; after the main loop the groups' accumulators
     static constexpr int ACC = MI * NJ * 16 * 256 * 4;           // bytes of one group's accumulators
     static constexpr int SMEM = KG * (2 * STAGE > ACC || KG == 1 ? 2 * STAGE : ACC);
 };
-
-__device__ __forceinline__ int slab_off(int r, int c) { return r * 64 + ((c ^ ((r >> 2) & 3)) << 4); }
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -302,79 +300,16 @@ void gemm_direct_kernel(DirectProblem p, int tiles_m, int tiles_n) {
         }
     }
 
-    // The groups' sums are added in the order of their K ranges; group g
-    // finishes accumulators r of [16 g / KG, 16 (g + 1) / KG) of every block.
-    constexpr int RG = 16 / KG;
-    float out[MI][NJ][RG];
-    if constexpr (KG == 1) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                for (int r = 0; r < RG; ++r) out[i][j][r] = acc[i][j][r];
-    } else {
-        f32x4* x = reinterpret_cast<f32x4*>(lds);  // [group][block][quad][thread]
-        constexpr int QG = 4 / KG;                 // quads of a block that one group finishes
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    x[((group * MI * NJ + i * NJ + j) * 4 + v) * 256 + t] =
-                        f32x4{acc[i][j][4 * v], acc[i][j][4 * v + 1], acc[i][j][4 * v + 2], acc[i][j][4 * v + 3]};
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                for (int v = 0; v < QG; ++v) {
-                    f32x4 sum = x[((i * NJ + j) * 4 + group * QG + v) * 256 + t];
-#pragma unroll
-                    for (int g = 1; g < KG; ++g) sum += x[((g * MI * NJ + i * NJ + j) * 4 + group * QG + v) * 256 + t];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) out[i][j][4 * v + e] = sum[e];
-                }
-    }
+    float out[MI][NJ][16 / KG];
+    sum_groups<KG, 256>(acc, out, lds, group, t);
 
-    // Epilogue: lane l holds column l % 32, rows 8 (r / 4) + 4 (l / 32) + r % 4 of a block
     const bool part = p.partial != nullptr;
     const int64_t ldc = part ? p.N : p.ldc;
     const float alpha = part ? 1.f : p.alpha, beta = part ? 0.f : p.beta;
-    const gfloat corner = (part ? (gfloat)p.partial + (int64_t)blockIdx.y * p.M * p.N : (gfloat)p.C) +
-                          (m0 + wm * 32 + 4 * fk + group * (32 / KG)) * ldc + n0 + wn * 32 + fr;
-    auto finish = [&](auto full_tag) __attribute__((always_inline)) {
-        constexpr bool FULL = decltype(full_tag)::value;
-        const int rl = rows - (wm * 32 + 4 * fk + group * (32 / KG)), cl = cols - (wn * 32 + fr);   // rows and columns from `corner` on
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                if (!FULL && 64 * j >= cl) continue;
-                const gfloat c = corner + (64 * i * ldc + 64 * j);
-                float old[RG];
-                if (beta != 0.f) {
-#pragma unroll
-                    for (int r = 0; r < RG; ++r) {
-                        const int dr = (r >> 2) * 8 + (r & 3);
-                        old[r] = FULL || 64 * i + dr < rl ? c[dr * ldc] : 0.f;
-                    }
-                }
-#pragma unroll
-                for (int r = 0; r < RG; ++r) {
-                    const int dr = (r >> 2) * 8 + (r & 3);
-                    if (FULL || 64 * i + dr < rl) {
-                        float v = alpha * out[i][j][r];
-                        if (beta != 0.f) v = __builtin_fmaf(beta, old[r], v);
-                        c[dr * ldc] = v;
-                    }
-                }
-            }
-    };
-    if (rows == BM && cols == BN) finish(std::true_type{});
-    else finish(std::false_type{});
+    const int r0 = wm * 32 + 4 * fk + group * (32 / KG), c0 = wn * 32 + fr;
+    const gfloat corner = (part ? (gfloat)p.partial + (int64_t)blockIdx.y * p.M * p.N : (gfloat)p.C) + (m0 + r0) * ldc + n0 + c0;
+    if (rows == BM && cols == BN) store_blocks<true, 64, 64>(out, corner, ldc, 0, 0, alpha, beta);
+    else store_blocks<false, 64, 64>(out, corner, ldc, rows - r0, cols - c0, alpha, beta);
 }
 
 template <typename Cfg, int WAVES>

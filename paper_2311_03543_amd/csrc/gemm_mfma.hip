@@ -29,12 +29,12 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "mfma_tile.h"
 
 namespace cmp {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef int intx8 __attribute__((ext_vector_type(8)));
 typedef int intx4 __attribute__((ext_vector_type(4)));
 typedef int intx2 __attribute__((ext_vector_type(2)));
@@ -49,31 +49,6 @@ constexpr size_t kSmem = (size_t)NBUF4 * STAGE4;   // 128 KiB
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
-// Byte offset of 16-byte chunk c of slab row r (the panel swizzle).  gfx950's
-// LDS serves a 16-byte-per-lane read 16 lanes at a time over 64 banks (256
-// bytes = 4 slab rows); the 16 rows one lane group of a fragment read touches
-// then occupy (r % 4, c ^ (r / 4) % 4): 16 distinct bank quads, no conflicts.
-__device__ __forceinline__ int slab_off(int r, int c) { return r * 64 + ((c ^ ((r >> 2) & 3)) << 4); }
-
-// s_waitcnt immediate: vmcnt <= vm (0..63), lgkmcnt <= lgkm (0..15), expcnt free.
-constexpr int waitcnt_imm(int vm, int lgkm) {
-    return (vm & 15) | ((vm >> 4) << 14) | (7 << 4) | (lgkm << 8);
-}
-
-// Stage barrier: this wave's LDS reads done, at most VM of its copies still
-// in flight (copies complete in issue order), then the workgroup barrier:
-// afterwards every wave's copies of the awaited stage have landed and every
-// wave's reads of the slot about to be refilled are complete.  The empty asm
-// statements keep the compiler from moving memory accesses across.
-template <int VM>
-__device__ __forceinline__ void stage_barrier() {
-    static_assert(VM >= 0 && VM <= 63, "vmcnt range");
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(waitcnt_imm(VM, 0));
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
 // One 1 KiB linear copy, part P (0..3) of this wave's quarter (4 KiB) of a
 // slab.  `src` already holds the wave's and the lane's offset (wave * 4 KiB +
 // 16 lane), `dst` the wave's slab quarter; lane l lands at dst + 1024 P + 16 l.
@@ -81,20 +56,6 @@ template <int P>
 __device__ __forceinline__ void dma_part(const uint8_t* src, uint8_t* dst) {
     static_assert(P >= 0 && P < 4, "part of a 4 KiB quarter");
     __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)dst, 16, P * 1024, 0);
-}
-
-// The main loops pin their instruction order explicitly: each MFMA is
-// followed by the memory instructions that ride under it, and a
-// sched_barrier after each group keeps the scheduler from clustering them.
-__device__ __forceinline__ void pin() { __builtin_amdgcn_sched_barrier(0); }
-
-// f(integral_constant<int, I>) for I = B .. E - 1, unrolled at compile time.
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
 }
 
 // 32 x 32 accumulator block layout: lane l holds column l % 32 and rows
@@ -245,7 +206,7 @@ void gemm_bf16_ring_kernel(int64_t M, int64_t N, int nkb, float alpha, const uin
 #pragma unroll
     for (int f = 0; f < 8; ++f) read(0, 0, f, fa[0], fb[0]);
     int cur = 0;
-    pin();
+    sched_pin();
     auto one_stage = [&](auto more_tag) {
         constexpr bool MORE = decltype(more_tag)::value;
         const int nxt = cur + 1 == NRING ? 0 : cur + 1;
@@ -254,17 +215,17 @@ void gemm_bf16_ring_kernel(int64_t M, int64_t N, int nkb, float alpha, const uin
         for (int q = 0; q < 16; ++q) {
             mfma(q, fa[0], fb[0]);
             if (q < 8) read(cur, 1, q, fa[1], fb[1]);
-            pin();
+            sched_pin();
         }
         // ks 1
 #pragma unroll
         for (int q = 0; q < PRE; ++q) mfma(q, fa[1], fb[1]);
-        pin();
+        sched_pin();
         if constexpr (MORE) {
             stage_barrier<8 * (NRING - 2)>();
             prepare();
         }
-        pin();
+        sched_pin();
         static_for<PRE, 16>([&](auto q_tag) {
             constexpr int Q = decltype(q_tag)::value;
             mfma(Q, fa[1], fb[1]);
@@ -272,7 +233,7 @@ void gemm_bf16_ring_kernel(int64_t M, int64_t N, int nkb, float alpha, const uin
                 copy(std::integral_constant<int, Q - PRE>{});
                 read(nxt, 0, Q - PRE, fa[0], fb[0]);
             }
-            pin();
+            sched_pin();
         });
         cur = nxt;
     };
@@ -396,7 +357,7 @@ __device__ __forceinline__ void bf16x3_tile(uint8_t* smem, int64_t M, int64_t N,
         read(0, 0, std::integral_constant<int, read_order(decltype(k)::value)>{}, F0);
     });
     int cur = 0;
-    pin();
+    sched_pin();
     // One stage = two sub-steps of NM MFMAs over slot `cur`:
     //   ks 0: MFMA q on F0; after MFMA ST k, read fragment read_order(k) of ks 1 into F1
     //   ks 1: one MFMA on F1; stage barrier (stage s + 1 landed, slot `cur`
@@ -411,15 +372,15 @@ __device__ __forceinline__ void bf16x3_tile(uint8_t* smem, int64_t M, int64_t N,
             mfma(q, F0);
             if constexpr (Q % ST == 0 && Q / ST < 16)
                 read(cur, 1, std::integral_constant<int, read_order(Q / ST)>{}, F1);
-            pin();
+            sched_pin();
         });
         mfma(std::integral_constant<int, 0>{}, F1);
-        pin();
+        sched_pin();
         if constexpr (MORE) {
             stage_barrier<0>();
             prepare();
         }
-        pin();
+        sched_pin();
         static_for<1, NM>([&](auto q) {
             constexpr int m = decltype(q)::value - 1;
             mfma(q, F1);
@@ -427,7 +388,7 @@ __device__ __forceinline__ void bf16x3_tile(uint8_t* smem, int64_t M, int64_t N,
                 read(nxt, 0, std::integral_constant<int, read_order(m / ST)>{}, F0);
                 copy(std::integral_constant<int, m / ST>{});
             }
-            pin();
+            sched_pin();
         });
         cur = nxt;
     };
@@ -631,7 +592,7 @@ void gemm_fp8r_fused_kernel(int64_t M, int64_t N, int nkb, float alpha,
     static_for<0, 8>([&](auto h) { read(0, I0{}, h); });
     static_for<0, 8>([&](auto h) { read(0, I1{}, h); });
     int cur = 0;
-    pin();
+    sched_pin();
 
     auto one_stage = [&](auto more_tag) {
         constexpr bool MORE = decltype(more_tag)::value;
@@ -642,40 +603,40 @@ void gemm_fp8r_fused_kernel(int64_t M, int64_t N, int nkb, float alpha,
             constexpr int k = decltype(q)::value;
             if constexpr (k < 8) read(cur, I3{}, std::integral_constant<int, k>{});
             else read(cur, I2{}, std::integral_constant<int, k - 8>{});
-            pin();
+            sched_pin();
         });
         if constexpr (MORE) {
             stage_barrier<0>();                 // stage s + 1 landed, slot `cur` free
             prepare();
         }
-        pin();
+        sched_pin();
         // q.r; the copies of stage s + 2 under it
         static_for<0, 16>([&](auto q) {
             mfma(I1{}, q);
             if constexpr (MORE) copy(q);
-            pin();
+            sched_pin();
         });
         if constexpr (MORE) {
             unpack_next();                      // stage s + 1's scales (words loaded a stage ago)
             load_scale_words();                 // stage s + 2's words
         }
-        pin();
+        sched_pin();
         // r.q; read Aq of stage s + 1 under it
         static_for<0, 16>([&](auto q) {
             mfma(I2{}, q);
             constexpr int k = decltype(q)::value;
             if constexpr (MORE && k < 8) read(nxt, I0{}, std::integral_constant<int, k>{});
-            pin();
+            sched_pin();
         });
         // r.r; read Bq of stage s + 1 under it
         static_for<0, 16>([&](auto q) {
             mfma(I3{}, q);
             constexpr int k = decltype(q)::value;
             if constexpr (MORE && k < 8) read(nxt, I1{}, std::integral_constant<int, k>{});
-            pin();
+            sched_pin();
         });
         if constexpr (MORE) advance_scales();
-        pin();
+        sched_pin();
         cur = nxt;
     };
     for (int s = 0; s + 1 < steps; ++s) one_stage(std::true_type{});
@@ -836,7 +797,7 @@ void gemm_fp6x3_fused_kernel(int64_t M, int64_t N, int nkb, float alpha,
         SB[b] = read_scale(0, 1, b);
     }
     int cur = 0;
-    pin();
+    sched_pin();
 
     auto one_stage = [&](auto more_tag) {
         constexpr bool MORE = decltype(more_tag)::value;
@@ -847,21 +808,21 @@ void gemm_fp6x3_fused_kernel(int64_t M, int64_t N, int nkb, float alpha,
             constexpr int k = decltype(q)::value;
             if constexpr (k < 8) read(cur, I3{}, std::integral_constant<int, k>{});
             else read(cur, I2{}, std::integral_constant<int, k - 8>{});
-            pin();
+            sched_pin();
         });
         if constexpr (MORE) {
             stage_barrier<13 * (F6NBUF - 2)>(); // stage s + 1 landed, slot `cur` free
             prepare();
         }
-        pin();
+        sched_pin();
         // h.l; the copies of stage s + F6NBUF under it
         static_for<0, 16>([&](auto q) {
             mfma(I1{}, q);
             constexpr int k = decltype(q)::value;
             if constexpr (MORE && k < 13) copy(q);
-            pin();
+            sched_pin();
         });
-        pin();
+        sched_pin();
         // l.h; Ah of stage s + 1 under the first 8 MFMAs; Bh block j and B
         // scale j of stage s + 1 once MFMA 4 j + 3 (the last one reading them)
         // has issued; A scale i of stage s + 1 once MFMA 12 + i has issued
@@ -875,9 +836,9 @@ void gemm_fp6x3_fused_kernel(int64_t M, int64_t N, int nkb, float alpha,
                 SB[k / 4] = read_scale(nxt, 1, k / 4);
             }
             if constexpr (MORE && k >= 12) SA[k - 12] = read_scale(nxt, 0, k - 12);
-            pin();
+            sched_pin();
         });
-        pin();
+        sched_pin();
         cur = nxt;
     };
     for (int s = 0; s + 1 < steps; ++s) one_stage(std::true_type{});
@@ -887,20 +848,6 @@ void gemm_fp6x3_fused_kernel(int64_t M, int64_t N, int nkb, float alpha,
         epilogue(acc, M, N, m0, n0, wm, wn, lane, 1.f, 0.f, P + (size_t)blockIdx.y * M * N, N);
     else
         epilogue(acc, M, N, m0, n0, wm, wn, lane, alpha, beta, C, ldc);
-}
-
-// The kernels use more than the default 64 KiB of dynamic LDS; the limit is a
-// per-device function attribute, set once on each device the library runs on.
-template <class Kernel>
-hipError_t allow_lds(Kernel kernel, std::atomic<uint64_t>& done, size_t bytes = kSmem) {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
-    if (bit && (done.load(std::memory_order_relaxed) & bit)) return hipSuccess;
-    e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
-    return e;
 }
 
 // Split-K: `splits` > 1 runs the K range in that many slices (grid y), each
@@ -956,13 +903,13 @@ hipError_t launch_gemm_bf16_tn(int64_t M, int64_t N, int64_t Kp, int nterms, flo
     const dim3 grid(tiles_m * tiles_n, splits);
     if (nterms == 3) {
         static std::atomic<uint64_t> lds_x3{0};
-        if (hipError_t e = allow_lds(gemm_bf16x3_slab4_kernel, lds_x3)) return e;
+        if (hipError_t e = allow_lds(gemm_bf16x3_slab4_kernel, lds_x3, kSmem)) return e;
         hipLaunchKernelGGL(gemm_bf16x3_slab4_kernel, grid, dim3(THREADS), kSmem, stream, M, N, nkb,
                            alpha, (const uint8_t*)Ah, (const uint8_t*)Al, (const uint8_t*)Bh,
                            (const uint8_t*)Bl, beta, C, ldc, tiles_m, tiles_n, kbs, P);
     } else {
         static std::atomic<uint64_t> lds_x1{0};
-        if (hipError_t e = allow_lds(gemm_bf16_ring_kernel, lds_x1)) return e;
+        if (hipError_t e = allow_lds(gemm_bf16_ring_kernel, lds_x1, kSmem)) return e;
         hipLaunchKernelGGL(gemm_bf16_ring_kernel, grid, dim3(THREADS), kSmem, stream, M, N, nkb,
                            alpha, (const uint8_t*)Ah, (const uint8_t*)Bh, beta, C, ldc, tiles_m,
                            tiles_n, kbs, P);
@@ -988,7 +935,7 @@ hipError_t launch_gemm_fp8r_tn(int64_t M, int64_t N, int64_t Kp, float alpha, co
                                float* partial, hipStream_t stream) {
     if (Kp % kFp8TileK || Kp <= 0) return hipErrorInvalidValue;
     static std::atomic<uint64_t> lds_f8{0};
-    if (hipError_t e = allow_lds(gemm_fp8r_fused_kernel, lds_f8)) return e;
+    if (hipError_t e = allow_lds(gemm_fp8r_fused_kernel, lds_f8, kSmem)) return e;
     const int tiles_m = (int)((M + TM - 1) / TM), tiles_n = (int)((N + TN - 1) / TN);
     const int nkb = (int)(Kp / kPanelRowBytes);
     if (splits < 1 || (splits > 1 && !partial)) return hipErrorInvalidValue;

@@ -147,9 +147,9 @@ hipError_t launch_gemm_bf16_tn(int64_t M, int64_t N, int64_t Kp, int nterms, flo
 // The same product straight from the FP32 operands, without images
 // (gemm_direct.hip), where that is expected to be faster: tile 0 = use the
 // images; otherwise the tile (128, or 127: 128 with one group over K; 64, or 63:
-// 64 with more groups over K) and the K slices (> 1: slice s writes its raw sum to partial + s * M * N, as
-// above).  image_splits: the slices the image form would take; ws_bytes: room
-// for partial sums.
+// 64 with more groups over K) and the K slices (> 1: slice s writes its raw sum
+// to partial + s * M * N, as above).  image_splits: the slices the image form
+// would take; ws_bytes: room for partial sums.
 struct DirectPlan {
     int tile = 0, slices = 1;
 };
@@ -168,6 +168,18 @@ hipError_t launch_gemm_fp8r_tn(int64_t M, int64_t N, int64_t Kp, float alpha,
                                const uint8_t* Bsq, const uint8_t* Bsr,
                                float beta, float* C, int64_t ldc, int splits, float* partial,
                                hipStream_t stream);
+// The same over smaller tiles (gemm_fp8r_tiles.hip), where that is expected to be
+// faster: tile 0 = use the kernel above; otherwise 256 (x 128), 64 or 63 (64, with
+// a workgroup's K range not divided among groups of waves), and the K slices (at
+// most image_splits, those of the kernel above).
+struct Fp8rPlan {
+    int tile = 0, slices = 1;
+};
+Fp8rPlan fp8r_plan(int64_t M, int64_t N, int64_t Kp, int image_splits);
+hipError_t launch_gemm_fp8r_tiles(const Fp8rPlan& plan, int64_t M, int64_t N, int64_t Kp, float alpha, const uint8_t* Aq,
+                                  const uint8_t* Ar, const uint8_t* Asq, const uint8_t* Asr, const uint8_t* Bq,
+                                  const uint8_t* Br, const uint8_t* Bsq, const uint8_t* Bsr, float beta, float* C,
+                                  int64_t ldc, float* partial, hipStream_t stream);
 
 // MX FP6 with one residual level: C = alpha * (Ah.Bh + Ah.Bl + Al.Bh) + beta * C
 // over the MX FP6 images of launch_quant_mx6 (codes Ah / Al and scales As of

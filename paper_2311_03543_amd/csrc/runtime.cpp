@@ -632,6 +632,17 @@ int run_images(cmp_ctx* c, int kind, const cmp_gemm_args* a, void* ws, hipStream
                                      lo ? (uint16_t*)I.at(ws, 2) : nullptr, (uint16_t*)I.at(ws, 1),
                                      lo ? (uint16_t*)I.at(ws, 3) : nullptr, a->beta, a->C, a->ldc,
                                      splits, partial, s);
+    } else if (const cmp::Fp8rPlan d = kind == kImgFp8r && c->split_k == 0 ? cmp::fp8r_plan(a->M, a->N, I.Kp, splits)
+                                                                           : cmp::Fp8rPlan{};
+               d.tile) {                   // a forced slice count asks for the 256 x 256 tiles
+        {
+            KTimer kt(c, s, "gemm_fp8r_tiles");
+            e = cmp::launch_gemm_fp8r_tiles(d, a->M, a->N, I.Kp, a->alpha, I.at(ws, 0), I.at(ws, 1), I.at(ws, 4),
+                                            I.at(ws, 5), I.at(ws, 2), I.at(ws, 3), I.at(ws, 6), I.at(ws, 7), a->beta,
+                                            a->C, a->ldc, partial, s);
+        }
+        if (e != hipSuccess) return CMP_EHIP;
+        return finish_split(c, a, d.slices, partial, s);
     } else if (kind == kImgFp8r) {
         KTimer kt(c, s, "gemm_fp8r_tn");
         e = cmp::launch_gemm_fp8r_tn(a->M, a->N, I.Kp, a->alpha, I.at(ws, 0), I.at(ws, 1), I.at(ws, 4),
