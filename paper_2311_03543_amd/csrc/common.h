@@ -148,8 +148,11 @@ struct TileClaims {
         const int wgs = ((int)gridDim.x - x + kXcds - 1) / kXcds;
         return wgs < size(x) ? wgs : size(x);
     }
-    // Claim the next entry of the own list (thread 0): the answer arrives under
-    // the current tile.  The opaque zero keeps the compiler from waiting for it here.
+    // Claim the next entry of the own list (thread 0).  Called as a tile's stores
+    // begin, so that the answer arrives under them; claimed at the start of a long
+    // tile, an entry would wait for it while other workgroups idle (40 bf16x3
+    // problems up to 512, one tile per workgroup: 79 us instead of 54).  The opaque
+    // zero keeps the compiler from waiting for it here.
     __device__ __forceinline__ void prefetch() {
         int zero = 0;
         asm volatile("" : "+v"(zero));

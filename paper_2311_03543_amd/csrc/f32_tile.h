@@ -104,8 +104,10 @@ __device__ __forceinline__ void f32_stage_barrier() {
 // Cfg::SMEM_FLOATS floats, 256-byte aligned; it may be reused after a
 // workgroup barrier.  vec: A and B allow 16-byte loads (16-byte aligned, lda
 // and ldb multiples of 4).  alpha == 0 or K == 0 never reads A or B.
-template <typename Cfg>
-__device__ __forceinline__ void f32_tile(const F32Problem& p, int64_t m0, int64_t n0, bool vec, float* smem) {
+// before_stores() runs once between the two.
+template <typename Cfg, class Hook>
+__device__ __forceinline__ void f32_tile(const F32Problem& p, int64_t m0, int64_t n0, bool vec, float* smem,
+                                         Hook&& before_stores) {
     constexpr int BK = Cfg::BK, BN = Cfg::BN, MF = Cfg::MF, NS = Cfg::NS, MI = Cfg::MI, NJ = Cfg::NJ;
     constexpr int QA = Cfg::QA, QB = Cfg::QB, CPR = Cfg::CPR, CPB = Cfg::CPB, CH = Cfg::CH;
     typedef const __attribute__((address_space(1))) void* gptr;
@@ -309,6 +311,7 @@ __device__ __forceinline__ void f32_tile(const F32Problem& p, int64_t m0, int64_
             stage(std::false_type{}, std::integral_constant<bool, MI * NJ == 1>{}, std::true_type{});
     }
 
+    before_stores();
     // Epilogue: C = alpha * acc + beta * C (C not read when beta == 0).  Lane l
     // holds column l % MF; rows 8 (r / 4) + 4 (l / 32) + r % 4 of a 32 x 32
     // block, 4 (l / 16) + r of a 16 x 16 one.  A block's old values are all

@@ -29,12 +29,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
     __shared__ __attribute__((aligned(256))) float smem[Cfg::SMEM_FLOATS];
     int tm, tn;
     grouped_tile(xcd_remap(blockIdx.x, tiles_m * tiles_n), tiles_m, tiles_n, 8, tm, tn);
-    f32_tile<Cfg>(p, (int64_t)tm * Cfg::BM, (int64_t)tn * Cfg::BN, vec, smem);
+    f32_tile<Cfg>(p, (int64_t)tm * Cfg::BM, (int64_t)tn * Cfg::BN, vec, smem, [] {});
 }
 
 // Persistent grouped kernel over the tile lists of `q` (common.h): each
-// workgroup works through tiles, claiming the next one while it computes.  A
-// list holds its pieces in decreasing order of K, so the longest tiles go first.
+// workgroup works through tiles.  A list holds its pieces in decreasing order of
+// K, so the longest tiles go first.  The next tile is claimed where the stores of
+// one begin, but where a 64 x 64 tile begins, whose few stores do not cover the
+// answer (512 problems up to 512: 111 us, claimed late 118); 128 x 128 tiles are
+// long enough that an entry claimed early would wait for one while other
+// workgroups idle (124 us, claimed late 114).
 // Workgroups per CU a configuration is built for: the LDS of its ring (160 KiB
 // a CU) and the accumulators allow no more.  A tile's fixed costs (first copies
 // from HBM, the stores of C) hide under the other workgroups of the CU.
@@ -54,15 +58,19 @@ void gemm_f32_grouped_kernel(const GroupedDesc* __restrict__ desc, int count, Ti
     typedef const __attribute__((address_space(1))) GroupedDesc* gdesc;
     const gdesc dg = (gdesc)desc;
     TileClaims claims(q, counters);
+    constexpr bool EARLY = Cfg::MI * Cfg::NJ == 1;
     for (int tile = claims.first(&slot); tile >= 0; tile = claims.next(&slot)) {
-        claims.prefetch();
+        if (EARLY) claims.prefetch();
         const int lo = wave_find_last(count, tile, [&](int i) { return dg[i].tile_start; });
         const int tiles_n = dg[lo].tiles_n;
         const int local = tile - dg[lo].tile_start + dg[lo].tile_first;
         const int tm = local / tiles_n, tn = local - (local / tiles_n) * tiles_n;
         const F32Problem p{dg[lo].M, dg[lo].N, dg[lo].K, dg[lo].lda, dg[lo].ldb, dg[lo].ldc,
                             dg[lo].alpha, dg[lo].beta, dg[lo].A, dg[lo].B, dg[lo].C};
-        f32_tile<Cfg>(p, (int64_t)tm * Cfg::BM, (int64_t)tn * Cfg::BN, dg[lo].vec != 0, smem);
+        f32_tile<Cfg>(p, (int64_t)tm * Cfg::BM, (int64_t)tn * Cfg::BN, dg[lo].vec != 0, smem,
+                      [&]() __attribute__((always_inline)) {
+                          if (!EARLY) claims.prefetch();
+                      });
         // claims.next starts with a barrier: the ring is free for the next tile
     }
     claims.finish();

@@ -273,11 +273,13 @@ constexpr int read_order(int k) {
 // 128 KiB LDS ring.  P != nullptr: the raw partial sums go to P (a split-K
 // slice, row pitch N); otherwise C = alpha * acc + beta * C.  Every copy has
 // landed when it returns (the ring may be reused after a workgroup barrier).
+// before_stores() runs once between the products and the stores.
+template <class Hook>
 __device__ __forceinline__ void bf16x3_tile(uint8_t* smem, int64_t M, int64_t N, int nkb, float alpha,
                                             const uint8_t* __restrict__ Ah, const uint8_t* __restrict__ Al,
                                             const uint8_t* __restrict__ Bh, const uint8_t* __restrict__ Bl,
                                             float beta, float* __restrict__ C, int64_t ldc, int tm, int tn,
-                                            int kb0, int steps, float* __restrict__ P) {
+                                            int kb0, int steps, float* __restrict__ P, Hook&& before_stores) {
     // LDS ring: slot i = four slabs at i * STAGE4
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);   // wave-uniform (SGPR)
@@ -395,6 +397,7 @@ __device__ __forceinline__ void bf16x3_tile(uint8_t* smem, int64_t M, int64_t N,
     for (int s = 0; s + 1 < steps; ++s) one_stage(std::true_type{});
     one_stage(std::false_type{});
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));   // drain the trailing copies
+    before_stores();
     if (P)   // split-K: raw partial sums of this split, reduced by splitk_reduce_kernel
         epilogue(acc, M, N, m0, n0, wm, wn, lane, 1.f, 0.f, P, N);
     else
@@ -414,12 +417,12 @@ void gemm_bf16x3_slab4_kernel(int64_t M, int64_t N, int nkb, float alpha,
     const int kb0 = (int)blockIdx.y * kb_split;
     const int steps = nkb - kb0 < kb_split ? nkb - kb0 : kb_split;
     bf16x3_tile(smem, M, N, nkb, alpha, Ah, Al, Bh, Bl, beta, C, ldc, tm, tn, kb0, steps,
-                P ? P + (size_t)blockIdx.y * M * N : nullptr);
+                P ? P + (size_t)blockIdx.y * M * N : nullptr, [] {});
 }
 
 // Many bf16x3 problems in one persistent launch (the grouped plan's MFMA
 // configuration) over the tile lists of `q` (common.h): each workgroup works
-// through 256 x 256 tiles, claiming the next one while it computes.  The
+// through 256 x 256 tiles, claiming the next one as it stores.  The
 // claimed tile passes through the 16 bytes past the ring, so the LDS request
 // is kSmem + 16.
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
@@ -431,7 +434,6 @@ void gemm_bf16x3_grouped_kernel(const GroupedMfmaDesc* __restrict__ desc, int co
     const gdesc dg = (gdesc)desc;
     TileClaims claims(q, counters);
     for (int tile = claims.first(slot); tile >= 0; tile = claims.next(slot)) {
-        claims.prefetch();
         const int lo = wave_find_last(count, tile, [&](int i) { return dg[i].tile_start; });
         const int local = tile - dg[lo].tile_start + dg[lo].tile_first;
         const int tn_count = dg[lo].tiles_n;
@@ -439,7 +441,8 @@ void gemm_bf16x3_grouped_kernel(const GroupedMfmaDesc* __restrict__ desc, int co
         const int nkb = (int)(dg[lo].Kp * 2 / kPanelRowBytes);
         bf16x3_tile(smem, dg[lo].M, dg[lo].N, nkb, dg[lo].alpha, (const uint8_t*)dg[lo].ah,
                     (const uint8_t*)dg[lo].al, (const uint8_t*)dg[lo].bh, (const uint8_t*)dg[lo].bl,
-                    dg[lo].beta, dg[lo].C, dg[lo].ldc, tm, tn, 0, nkb, nullptr);
+                    dg[lo].beta, dg[lo].C, dg[lo].ldc, tm, tn, 0, nkb, nullptr,
+                    [&]() __attribute__((always_inline)) { claims.prefetch(); });
         // claims.next starts with a barrier: the ring is free for the next tile
     }
     claims.finish();
