@@ -150,8 +150,7 @@ struct TileClaims {
     }
     // Claim the next entry of the own list (thread 0).  Called as a tile's stores
     // begin, so that the answer arrives under them; claimed at the start of a long
-    // tile, an entry would wait for it while other workgroups idle (40 bf16x3
-    // problems up to 512, one tile per workgroup: 79 us instead of 54).  The opaque
+    // tile, an entry would wait for it while other workgroups idle.  The opaque
     // zero keeps the compiler from waiting for it here.
     __device__ __forceinline__ void prefetch() {
         int zero = 0;

@@ -273,13 +273,11 @@ constexpr int read_order(int k) {
 // 128 KiB LDS ring.  P != nullptr: the raw partial sums go to P (a split-K
 // slice, row pitch N); otherwise C = alpha * acc + beta * C.  Every copy has
 // landed when it returns (the ring may be reused after a workgroup barrier).
-// before_stores() runs once between the products and the stores.
-template <class Hook>
 __device__ __forceinline__ void bf16x3_tile(uint8_t* smem, int64_t M, int64_t N, int nkb, float alpha,
                                             const uint8_t* __restrict__ Ah, const uint8_t* __restrict__ Al,
                                             const uint8_t* __restrict__ Bh, const uint8_t* __restrict__ Bl,
                                             float beta, float* __restrict__ C, int64_t ldc, int tm, int tn,
-                                            int kb0, int steps, float* __restrict__ P, Hook&& before_stores) {
+                                            int kb0, int steps, float* __restrict__ P) {
     // LDS ring: slot i = four slabs at i * STAGE4
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);   // wave-uniform (SGPR)
@@ -397,7 +395,6 @@ __device__ __forceinline__ void bf16x3_tile(uint8_t* smem, int64_t M, int64_t N,
     for (int s = 0; s + 1 < steps; ++s) one_stage(std::true_type{});
     one_stage(std::false_type{});
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));   // drain the trailing copies
-    before_stores();
     if (P)   // split-K: raw partial sums of this split, reduced by splitk_reduce_kernel
         epilogue(acc, M, N, m0, n0, wm, wn, lane, 1.f, 0.f, P, N);
     else
@@ -417,35 +414,52 @@ void gemm_bf16x3_slab4_kernel(int64_t M, int64_t N, int nkb, float alpha,
     const int kb0 = (int)blockIdx.y * kb_split;
     const int steps = nkb - kb0 < kb_split ? nkb - kb0 : kb_split;
     bf16x3_tile(smem, M, N, nkb, alpha, Ah, Al, Bh, Bl, beta, C, ldc, tm, tn, kb0, steps,
-                P ? P + (size_t)blockIdx.y * M * N : nullptr, [] {});
+                P ? P + (size_t)blockIdx.y * M * N : nullptr);
 }
 
 // Many bf16x3 problems in one persistent launch (the grouped plan's MFMA
-// configuration) over the tile lists of `q` (common.h): each workgroup works
-// through 256 x 256 tiles, claiming the next one as it stores.  The
-// claimed tile passes through the 16 bytes past the ring, so the LDS request
-// is kSmem + 16.
+// configuration): each workgroup works through 256 x 256 tiles of the
+// concatenated list, workgroup b starting with tile b and claiming each further
+// one from counters[0].  One list for the whole card, not one per XCD: there are
+// only two or three tiles per CU, each reads 256-row panels, and an even finish is
+// worth more than what the tiles of a problem share in an L2 (250 problems up to
+// 512: this kernel 81 us, with a list per XCD 90).  The last workgroup to finish,
+// told by counters[kQueuePitch], zeroes both for the next launch.  The claimed
+// tile passes through the 16 bytes past the ring, so the LDS request is kSmem + 16.
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void gemm_bf16x3_grouped_kernel(const GroupedMfmaDesc* __restrict__ desc, int count, TileQueues q,
+void gemm_bf16x3_grouped_kernel(const GroupedMfmaDesc* __restrict__ desc, int count, int total_tiles,
                                 unsigned* __restrict__ counters) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    int* slot = reinterpret_cast<int*>(smem + kSmem);
+    int* next_tile = reinterpret_cast<int*>(smem + kSmem);
     typedef const __attribute__((address_space(1))) GroupedMfmaDesc* gdesc;
     const gdesc dg = (gdesc)desc;
-    TileClaims claims(q, counters);
-    for (int tile = claims.first(slot); tile >= 0; tile = claims.next(slot)) {
-        const int lo = wave_find_last(count, tile, [&](int i) { return dg[i].tile_start; });
-        const int local = tile - dg[lo].tile_start + dg[lo].tile_first;
+    for (int tile = blockIdx.x; tile < total_tiles;) {
+        int lo = 0, hi = count - 1;            // last problem whose first tile is <= tile
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (dg[mid].tile_start <= tile) lo = mid;
+            else hi = mid - 1;
+        }
+        const int local = tile - dg[lo].tile_start;
         const int tn_count = dg[lo].tiles_n;
         const int tm = local / tn_count, tn = local - tm * tn_count;
         const int nkb = (int)(dg[lo].Kp * 2 / kPanelRowBytes);
         bf16x3_tile(smem, dg[lo].M, dg[lo].N, nkb, dg[lo].alpha, (const uint8_t*)dg[lo].ah,
                     (const uint8_t*)dg[lo].al, (const uint8_t*)dg[lo].bh, (const uint8_t*)dg[lo].bl,
-                    dg[lo].beta, dg[lo].C, dg[lo].ldc, tm, tn, 0, nkb, nullptr,
-                    [&]() __attribute__((always_inline)) { claims.prefetch(); });
-        // claims.next starts with a barrier: the ring is free for the next tile
+                    dg[lo].beta, dg[lo].C, dg[lo].ldc, tm, tn, 0, nkb, nullptr);
+        __syncthreads();                       // every wave is done with the ring and next_tile
+        if (threadIdx.x == 0) {
+            const unsigned ticket = atomicAdd(counters, 1u);
+            const unsigned left = (unsigned)total_tiles - gridDim.x;   // grid <= total_tiles
+            *next_tile = ticket < left ? (int)(gridDim.x + ticket) : total_tiles;
+        }
+        __syncthreads();
+        tile = __builtin_amdgcn_readfirstlane(*next_tile);
     }
-    claims.finish();
+    // every claim of this workgroup has been answered
+    if (threadIdx.x == 0 && atomicAdd(counters + kQueuePitch, 1u) == gridDim.x - 1)
+        for (int i = 0; i < 2; ++i)
+            __hip_atomic_store(counters + i * kQueuePitch, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---------------------------------------------------------------------------
@@ -920,14 +934,14 @@ hipError_t launch_gemm_bf16_tn(int64_t M, int64_t N, int64_t Kp, int nterms, flo
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_bf16x3_grouped(const GroupedMfmaDesc* desc, int count, const TileQueues& q, int grid,
+hipError_t launch_gemm_bf16x3_grouped(const GroupedMfmaDesc* desc, int count, int total_tiles, int grid,
                                       unsigned* counters, hipStream_t stream) {
-    if (q.start[kXcds] <= 0) return hipSuccess;
-    if (grid < 1 || grid > q.start[kXcds] || !counters || !desc || count < 1) return hipErrorInvalidValue;
+    if (total_tiles <= 0) return hipSuccess;
+    if (grid < 1 || grid > total_tiles || !counters || !desc || count < 1) return hipErrorInvalidValue;
     static std::atomic<uint64_t> lds_g{0};
     if (hipError_t e = allow_lds(gemm_bf16x3_grouped_kernel, lds_g, kSmem + 16)) return e;
-    hipLaunchKernelGGL(gemm_bf16x3_grouped_kernel, dim3(grid), dim3(THREADS), kSmem + 16, stream, desc, count, q,
-                       counters);
+    hipLaunchKernelGGL(gemm_bf16x3_grouped_kernel, dim3(grid), dim3(THREADS), kSmem + 16, stream, desc, count,
+                       total_tiles, counters);
     return hipGetLastError();
 }
 

@@ -41,9 +41,9 @@ struct GroupedConfig {
 };
 // One problem of a grouped bf16x3 launch: the operands, the problem's
 // bf16 hi / lo panel images (Mp x Kp of A, Np x Kp of B^T, in the plan's
-// workspace), the pre-pass workgroups of A (ga) and B (gb) from pre_start on
-// (none in a problem's further pieces), and the piece's 256 x 256 tiles, as in
-// GroupedDesc.  vec: bit 0 A, bit 1 B can be read with 16-byte loads.
+// workspace), the pre-pass workgroups of A (ga) and B (gb) from pre_start on,
+// and the problem's first 256 x 256 tile in the concatenated list.  vec: bit 0 A,
+// bit 1 B can be read with 16-byte loads.
 struct GroupedMfmaDesc {
     int64_t M, N, K, lda, ldb, ldc, Mp, Np, Kp;
     float alpha, beta;
@@ -51,7 +51,7 @@ struct GroupedMfmaDesc {
     const float* B;
     float* C;
     uint16_t *ah, *al, *bh, *bl;
-    int ga, gb, pre_start, tile_start, tiles_n, vec, tile_first;
+    int ga, gb, pre_start, tile_start, tiles_n, vec;
 };
 constexpr int kNumGroupedConfigs = 10;
 extern const GroupedConfig kGroupedConfigs[kNumGroupedConfigs];
@@ -65,7 +65,7 @@ hipError_t launch_gemm_f32_grouped(int config, const GroupedDesc* desc, int coun
 // workgroups), then every problem's tiles in one persistent launch.
 hipError_t launch_split_grouped(const GroupedMfmaDesc* desc, int count, int64_t pre_total,
                                 hipStream_t stream);
-hipError_t launch_gemm_bf16x3_grouped(const GroupedMfmaDesc* desc, int count, const TileQueues& q, int grid,
+hipError_t launch_gemm_bf16x3_grouped(const GroupedMfmaDesc* desc, int count, int total_tiles, int grid,
                                       unsigned* counters, hipStream_t stream);
 // Resident workgroups per CU of the grouped kernel for a configuration.
 int grouped_blocks_per_cu(int config);

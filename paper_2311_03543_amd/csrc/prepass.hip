@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256) void split_pair_kernel(SplitPair p) {
 }
 
 // The hi / lo images of every problem of a grouped bf16x3 plan in one launch:
-// workgroup w belongs to the last piece p with desc[p].pre_start <= w (each
+// workgroup w belongs to the last problem p with desc[p].pre_start <= w (each
 // problem's A workgroups, ga, then B's, gb), one split_a chunk pass
 // or one split_bt tile per workgroup.  Only rows below M (A, whose idle
 // 64-row quarters get no workgroup) and the 64-row tiles that start below N

@@ -2571,16 +2571,19 @@ void free_plan_buffers(cmp_grouped_plan* pl) {
 
 // Descriptors, images and counters of the bf16x3 configuration.
 int build_mfma(cmp_ctx* c, cmp_grouped_plan* pl, const std::vector<cmp_gemm_args>& probs, hipStream_t s) {
-    std::vector<Piece> pieces;
-    if (int st = tile_lists(c, probs, cmp::kMfmaTileM, cmp::kMfmaTileN, &pieces, &pl->queues, &pl->count)) return st;
+    std::vector<int> order;
+    for (int i = 0; i < (int)probs.size(); ++i)
+        if (probs[i].M > 0 && probs[i].N > 0) order.push_back(i);
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+        if (probs[x].K != probs[y].K) return probs[x].K > probs[y].K;
+        return (double)probs[x].M * probs[x].N > (double)probs[y].M * probs[y].N;
+    });
     std::vector<cmp::GroupedMfmaDesc> d;
-    std::vector<size_t> img_off;              // per piece: offset of its problem's four images
-    std::vector<int64_t> placed(probs.size(), -1);
+    std::vector<size_t> img_off;              // per problem: offset of its four images
     size_t img_bytes = 0;
-    int64_t pre = 0;
-    int tiles = 0;
-    for (const Piece& p : pieces) {
-        const cmp_gemm_args& a = probs[p.problem];
+    int64_t pre = 0, tiles = 0;
+    for (int i : order) {
+        const cmp_gemm_args& a = probs[i];
         cmp::GroupedMfmaDesc g{};
         g.M = a.M; g.N = a.N; g.K = a.K;
         g.lda = a.lda; g.ldb = a.ldb; g.ldc = a.ldc;
@@ -2589,27 +2592,21 @@ int build_mfma(cmp_ctx* c, cmp_grouped_plan* pl, const std::vector<cmp_gemm_args
         g.Kp = round_up(a.K, cmp::kBf16TileK);
         g.alpha = a.alpha; g.beta = a.beta;
         g.A = a.A; g.B = a.B; g.C = a.C;
+        // A: one workgroup per 64-row quarter of a 256-row x 64-byte block below M
+        g.ga = (int)((a.M / 256 * 4 + (a.M % 256 + 63) / 64) * (g.Kp * 2 / 64));
+        g.gb = (int)(((a.N + 63) / 64) * (g.Kp / 64));   // the 64-row tiles of B^T below N
         g.pre_start = (int)pre;
-        g.tile_start = tiles;
-        g.tile_first = p.first;
+        g.tile_start = (int)tiles;
         g.tiles_n = (int)(g.Np / cmp::kMfmaTileN);
         g.vec = ((a.lda % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.A) & 15) == 0) ? 1 : 0) |
                 ((a.ldb % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.B) & 15) == 0) ? 2 : 0);
-        if (placed[p.problem] < 0) {          // the problem's first piece brings its pre-pass
-            // A: one workgroup per 64-row quarter of a 256-row x 64-byte block below M
-            const int64_t ga = (a.M / 256 * 4 + (a.M % 256 + 63) / 64) * (g.Kp * 2 / 64);
-            const int64_t gb = ((a.N + 63) / 64) * (g.Kp / 64);   // the 64-row tiles of B^T below N
-            pre += ga + gb;
-            // (a workgroup's copy offsets reach its panel's K blocks: 64 bytes of K x 256 rows each)
-            if (pre > INT32_MAX || g.Kp * 2 / 64 * 16384 > INT32_MAX)
-                return fail(c, CMP_EINVAL, "grouped bf16x3 launch too large");
-            g.ga = (int)ga;
-            g.gb = (int)gb;
-            placed[p.problem] = (int64_t)img_bytes;
-            img_bytes += (size_t)round_up(g.Mp * g.Kp * 2, 256) * 2 + (size_t)round_up(g.Np * g.Kp * 2, 256) * 2;
-        }
-        tiles += p.tiles;
-        img_off.push_back((size_t)placed[p.problem]);
+        pre += (int64_t)g.ga + g.gb;
+        tiles += (g.Mp / cmp::kMfmaTileM) * (g.Np / cmp::kMfmaTileN);
+        // (a workgroup's copy offsets reach its panel's K blocks: 64 bytes of K x 256 rows each)
+        if (pre > INT32_MAX || tiles > INT32_MAX || g.Kp * 2 / 64 * 16384 > INT32_MAX)
+            return fail(c, CMP_EINVAL, "grouped bf16x3 launch too large");
+        img_off.push_back(img_bytes);
+        img_bytes += (size_t)round_up(g.Mp * g.Kp * 2, 256) * 2 + (size_t)round_up(g.Np * g.Kp * 2, 256) * 2;
         d.push_back(g);
     }
     if (img_bytes) HIP_TRY(c, hipMalloc(&pl->images, img_bytes));
@@ -2622,9 +2619,11 @@ int build_mfma(cmp_ctx* c, cmp_grouped_plan* pl, const std::vector<cmp_gemm_args
         d[p].bl = reinterpret_cast<uint16_t*>(base + 2 * as + bs);
     }
     if (int st = upload_descs(c, pl, d, &pl->mdesc, s)) return st;
-    pl->pieces = (int)d.size();
+    pl->count = (int)d.size();
+    pl->pieces = pl->count;
+    pl->queues.start[cmp::kXcds] = (int)tiles;   // (one list)
     pl->pre_total = pre;
-    pl->grid = std::max(1, std::min(tiles, c->props.multiProcessorCount));   // one 128 KiB ring per CU
+    pl->grid = std::max(1, std::min((int)tiles, c->props.multiProcessorCount));   // one 128 KiB ring per CU
     return CMP_OK;
 }
 
@@ -2646,7 +2645,8 @@ hipError_t plan_launch(cmp_grouped_plan* pl, hipStream_t s) {
     if (pl->config == kGroupedMfma) {
         hipError_t e = cmp::launch_split_grouped(pl->mdesc, pl->pieces, pl->pre_total, s);
         if (e == hipSuccess)
-            e = cmp::launch_gemm_bf16x3_grouped(pl->mdesc, pl->pieces, pl->queues, pl->grid, pl->counters, s);
+            e = cmp::launch_gemm_bf16x3_grouped(pl->mdesc, pl->pieces, pl->queues.start[cmp::kXcds], pl->grid,
+                                                pl->counters, s);
         return e;
     }
     return cmp::launch_gemm_f32_grouped(pl->config, pl->desc, pl->pieces, pl->queues, pl->grid, pl->counters, s);
