@@ -57,7 +57,7 @@ def kernel_roofline(name: str, M: int, N: int, K: int):
         return "mfma", 3 * 2.0 * M * N * K, PEAK["bf16"], "TFLOP/s"
     if name in ("gemm_fp8r_tn", "gemm_fp8r_tiles"):
         return "mfma", 4 * 2.0 * M * N * K, PEAK["fp8"], "TFLOP/s"
-    if name == "gemm_fp6x3_tn":
+    if name in ("gemm_fp6x3_tn", "gemm_fp6x3_tiles"):
         return "mfma", 3 * 2.0 * M * N * K, PEAK["fp6"], "TFLOP/s"
     # pre-pass kernels: bytes read + written (HBM-bound)
     if name == "split_bf16_ab":       # both operands in one launch
@@ -81,6 +81,7 @@ KERNEL_SOURCES = {  # kernel name -> source file (relative to the repo root)
     "gemm_fp8r_tn": "paper_2311_03543_amd/csrc/gemm_mfma.hip",
     "gemm_fp8r_tiles": "paper_2311_03543_amd/csrc/gemm_fp8r_tiles.hip",
     "gemm_fp6x3_tn": "paper_2311_03543_amd/csrc/gemm_mfma.hip",
+    "gemm_fp6x3_tiles": "paper_2311_03543_amd/csrc/gemm_fp6x3_tiles.hip",
 }
 
 

@@ -20,7 +20,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcompar.so")
 LIB_SAN = os.path.join(HERE, "libcompar_san.so")
 SOURCES = ["runtime.cpp", "gemm_f32_simt.hip", "gemm_mfma.hip", "gemm_direct.hip", "gemm_fp8r_tiles.hip",
-           "prepass.hip", "mx6.hip", "freivalds.hip", "mlp.hip", "host_gemm.cpp"]
+           "gemm_fp6x3_tiles.hip", "prepass.hip", "mx6.hip", "freivalds.hip", "mlp.hip", "host_gemm.cpp"]
 ARCH = "gfx950"
 
 

@@ -189,6 +189,16 @@ hipError_t launch_gemm_fp6x3_tn(int64_t M, int64_t N, int64_t Kp, float alpha, c
                                 const uint8_t* Al, const uint8_t* As, const uint8_t* Bh,
                                 const uint8_t* Bl, const uint8_t* Bs, float beta, float* C,
                                 int64_t ldc, int splits, float* partial, hipStream_t stream);
+// The same over smaller tiles (gemm_fp6x3_tiles.hip), as fp8r_plan: tile 0 = the
+// kernel above; otherwise 128, 64 or 63 (64, with K not divided among groups).
+struct Fp6x3Plan {
+    int tile = 0, slices = 1;
+};
+Fp6x3Plan fp6x3_plan(int64_t M, int64_t N, int64_t Kp, int image_splits);
+hipError_t launch_gemm_fp6x3_tiles(const Fp6x3Plan& plan, int64_t M, int64_t N, int64_t Kp, float alpha,
+                                   const uint8_t* Ah, const uint8_t* Al, const uint8_t* As, const uint8_t* Bh,
+                                   const uint8_t* Bl, const uint8_t* Bs, float beta, float* C, int64_t ldc,
+                                   float* partial, hipStream_t stream);
 
 // C = alpha * (partial[0] + ... + partial[splits - 1]) + beta * C, summed in
 // that order (beta == 0 never reads C); splits >= 2.

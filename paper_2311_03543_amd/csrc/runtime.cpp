@@ -648,6 +648,15 @@ int run_images(cmp_ctx* c, int kind, const cmp_gemm_args* a, void* ws, hipStream
         e = cmp::launch_gemm_fp8r_tn(a->M, a->N, I.Kp, a->alpha, I.at(ws, 0), I.at(ws, 1), I.at(ws, 4),
                                      I.at(ws, 5), I.at(ws, 2), I.at(ws, 3), I.at(ws, 6), I.at(ws, 7),
                                      a->beta, a->C, a->ldc, splits, partial, s);
+    } else if (const cmp::Fp6x3Plan d = c->split_k == 0 ? cmp::fp6x3_plan(a->M, a->N, I.Kp, splits) : cmp::Fp6x3Plan{};
+               d.tile) {
+        {
+            KTimer kt(c, s, "gemm_fp6x3_tiles");
+            e = cmp::launch_gemm_fp6x3_tiles(d, a->M, a->N, I.Kp, a->alpha, I.at(ws, 0), I.at(ws, 1), I.at(ws, 4),
+                                             I.at(ws, 2), I.at(ws, 3), I.at(ws, 5), a->beta, a->C, a->ldc, partial, s);
+        }
+        if (e != hipSuccess) return CMP_EHIP;
+        return finish_split(c, a, d.slices, partial, s);
     } else {
         KTimer kt(c, s, "gemm_fp6x3_tn");
         e = cmp::launch_gemm_fp6x3_tn(a->M, a->N, I.Kp, a->alpha, I.at(ws, 0), I.at(ws, 1), I.at(ws, 4),
