@@ -269,7 +269,7 @@ Fp8rPlan fp8r_plan(int64_t M, int64_t N, int64_t Kp, int image_splits) {
         if (kb * (s - 1) >= nkb) continue;         // every slice non-empty
         const double n64 = tiles(64, 64) * s / 256;
         offer(n64 > 2 ? 63 : 64, s, 5 + (n64 <= 1 ? 1 : (n64 + ceil(n64)) / 2) * (0.24 * kb + 0.9) + reduce(s));
-        offer(256, s, 5 + ceil(tiles(256, 128) * s / 256) * (1.31 * kb + 3) + reduce(s));
+        offer(256, s, 5 + ceil(tiles(256, 128) * s / 256) * (1.31 * kb + 6) + reduce(s));
     }
     return best;
 }
