@@ -512,7 +512,7 @@ def selector_experiment(cx, pa, torch, args):
 def grouped_experiment(cx, pa, torch, args):
     """1024 problems, M, N, K log-uniform in [32, 1024] (seed 4), normal(0,1) FP32 operands.
     The separate launches run f32_simt per problem; the grouped plan's autotuner picks among the
-    FP32 SIMT tiles and the bf16x3 MFMA configuration (both in the 1e-5 class)."""
+    FP32 tiles and the bf16x3 MFMA configuration (both in the 1e-5 class)."""
     count = args.grouped_problems
     shapes = synth.log_uniform_shapes(count, 32, 1024, 4)
     g = torch.Generator(device="cuda").manual_seed(5)

@@ -280,9 +280,10 @@ int cmp_reserve(cmp_ctx *ctx, int64_t M, int64_t N, int64_t K);
  * four default built-ins; for other variants it uses the history's nearest
  * timed shape. */
 int cmp_register_builtin(cmp_ctx *ctx, const char *name, int *id);
-/* Slice count a call of built-in variant `id` of "gemm" would use for an
+/* Slice count of the 256 x 256 tiles of built-in variant `id` of "gemm" for an
  * M x N x K product under the current setting (1 for f32_simt and for
- * variants registered by the caller). */
+ * variants registered by the caller): what the workspace is sized for.  With
+ * no count forced a call may take smaller tiles and fewer slices. */
 int cmp_split_k(cmp_ctx *ctx, int id, int64_t M, int64_t N, int64_t K, int *splits);
 /* Admissible variants for ctx->tol as a bit mask (bit i = id i). */
 int cmp_admissible(cmp_ctx *ctx, const char *iface, const cmp_context *c, uint64_t *mask);
@@ -496,11 +497,11 @@ int cmp_prepass_images(cmp_ctx *ctx, int id, const cmp_gemm_args *args, void *ou
  * for the plan's lifetime) as ONE persistent kernel whose
  * workgroups take tiles of the concatenated tile list from a device counter
  * as they finish their previous one, problems ordered by decreasing K (the
- * longest tiles first).  A launch zeroes the plan's counter first (a one-lane
- * kernel on the same stream, no memset, so the pair can be captured), and two
+ * longest tiles first).  Each launch leaves the plan's counters zero for the
+ * next one (no memset, so it can be captured), and two
  * launches of one plan must not run at the same time (they would share the
- * counter and the problems' C).  A configuration is a tile shape and an
- * arithmetic, one of cmp_grouped_config_count(): the first ones are FP32 SIMT
+ * counters and the problems' C).  A configuration is a tile shape and an
+ * arithmetic, one of cmp_grouped_config_count(): the first ones are FP32
  * tiles, bit-identical to cmp_gemm_variant with "f32_simt" per problem; the
  * last one runs the "bf16x3" variant's arithmetic (one launch splitting every
  * problem's A and B into bf16 hi / lo images in a workspace the plan owns,

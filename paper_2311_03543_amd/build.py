@@ -32,8 +32,8 @@ def hipcc() -> str:
 
 
 def common_flags() -> list[str]:
-    # Packed FP32 instructions are disabled on purpose: the FP32 kernels use
-    # plain v_fma_f32 only.
+    # Packed FP32 instructions are disabled on purpose: scalar FP32 and matrix
+    # instructions only.
     return [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
             "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-result"]

@@ -2553,14 +2553,14 @@ int grouped_grid(cmp_ctx* c, int config, int total_tiles) {
     return std::max(1, std::min(total_tiles, per_cu * c->props.multiProcessorCount));
 }
 
-// The configurations after the FP32 SIMT tiles: kGroupedMfma runs every
+// The configurations after the FP32 tiles: kGroupedMfma runs every
 // problem with the bf16x3 variant's arithmetic (its pre-pass and its 256 x 256
 // MFMA tile), bit-identical to one unsplit bf16x3 call per problem.
 constexpr int kGroupedMfma = cmp::kNumGroupedConfigs;
 constexpr int kGroupedAll = kGroupedMfma + 1;
 
 // The bf16x3 configuration needs every problem to read A and B: alpha == 0 or
-// K == 0 (C = beta C, operands never read) is left to the SIMT configurations.
+// K == 0 (C = beta C, operands never read) is left to the FP32 configurations.
 bool mfma_eligible(const std::vector<cmp_gemm_args>& probs) {
     for (const auto& a : probs)
         if (a.M > 0 && a.N > 0 && (a.alpha == 0.f || a.K == 0)) return false;
