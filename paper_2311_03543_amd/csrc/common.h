@@ -134,6 +134,20 @@ struct TileQueues {
 constexpr int kQueuePitch = 16;                   // 64 bytes: one counter per cache line
 constexpr int kQueueWords = (kXcds + 1) * kQueuePitch;
 
+// The end of a workgroup of a launch that claimed from `lists` counters (thread
+// 0, all claims answered): the launch's last workgroup zeroes them.  The counter
+// of the done ones follows them and wraps at the grid size by itself, never
+// stored to: were two launches of the same counters to overlap, which is not
+// allowed, the last workgroup of all would still be one that wraps it, so the
+// next launch finds every counter zero.  (A stored zero could drop the other
+// launch's arrivals, and then every later launch zeroed the lists too early.)
+__device__ __forceinline__ void end_claims(unsigned* counters, int lists) {
+    const unsigned last = gridDim.x - 1;
+    if (threadIdx.x == 0 && atomicInc(counters + lists * kQueuePitch, last) == last)
+        for (int x = 0; x < lists; ++x)
+            __hip_atomic_store(counters + x * kQueuePitch, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 struct TileClaims {
     const TileQueues& q;
     unsigned* counters;
@@ -193,11 +207,7 @@ struct TileClaims {
     }
 
     // After the last tile: every claim of this workgroup has been answered.
-    __device__ __forceinline__ void finish() const {
-        if (threadIdx.x == 0 && atomicAdd(counters + kXcds * kQueuePitch, 1u) == gridDim.x - 1)
-            for (int x = 0; x <= kXcds; ++x)
-                __hip_atomic_store(counters + x * kQueuePitch, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    __device__ __forceinline__ void finish() const { end_claims(counters, kXcds); }
 
   private:
     __device__ __forceinline__ static int share(int* slot, int tile) {

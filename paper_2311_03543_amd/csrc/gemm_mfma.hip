@@ -432,7 +432,7 @@ void gemm_bf16x3_slab4_kernel(int64_t M, int64_t N, int nkb, float alpha,
 // only two or three tiles per CU, each reads 256-row panels, and an even finish is
 // worth more than what the tiles of a problem share in an L2 (250 problems up to
 // 512: this kernel 81 us, with a list per XCD 90).  The last workgroup to finish,
-// told by counters[kQueuePitch], zeroes both for the next launch.  The claimed
+// told by counters[kQueuePitch], zeroes it for the next launch.  The claimed
 // tile passes through the 16 bytes past the ring, so the LDS request is kSmem + 16.
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void gemm_bf16x3_grouped_kernel(const GroupedMfmaDesc* __restrict__ desc, int count, int total_tiles,
@@ -464,10 +464,7 @@ void gemm_bf16x3_grouped_kernel(const GroupedMfmaDesc* __restrict__ desc, int co
         __syncthreads();
         tile = __builtin_amdgcn_readfirstlane(*next_tile);
     }
-    // every claim of this workgroup has been answered
-    if (threadIdx.x == 0 && atomicAdd(counters + kQueuePitch, 1u) == gridDim.x - 1)
-        for (int i = 0; i < 2; ++i)
-            __hip_atomic_store(counters + i * kQueuePitch, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    end_claims(counters, 1);                   // every claim of this workgroup has been answered
 }
 
 // ---------------------------------------------------------------------------
