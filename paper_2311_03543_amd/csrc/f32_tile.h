@@ -27,8 +27,10 @@
 //   B  BK rows of BN floats; the chunk of a row is moved by a constant of
 //      k % 4 so that the k values one MFMA reads lie in different banks.
 // Aligned operands are copied 16 bytes a lane, others and the last, partial
-// stage 4 bytes a lane; k >= K reads a zero word instead, rows and columns
-// past the edge repeat the last one (their products are never stored).
+// stage 4 bytes a lane; k >= K reads a zero word instead, -0 for A and +0 for
+// B, whose product -0 leaves every sum as it is (+0 would turn a sum of -0 into
+// +0, so that C depended on the stage depth); rows and columns past the edge
+// repeat the last one (their products are never stored).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -83,8 +85,8 @@ struct F32Cfg {
     static_assert(BN >= (MF == 32 ? 64 : 32), "B rows hold the displaced chunks");
 };
 
-// A zero word for the copies past the end of K.
-static __device__ float f32_tile_zero[4] = {0.f, 0.f, 0.f, 0.f};
+// The zero words of A and of B for the copies past the end of K.
+static __device__ float f32_tile_zero[2] = {-0.f, 0.f};
 
 template <int VM>
 __device__ __forceinline__ void f32_stage_wait() {
@@ -177,19 +179,19 @@ __device__ __forceinline__ void f32_tile(const F32Problem& p, int64_t m0, int64_
         float* word = smem + (s % NS) * Cfg::STAGE + wave * 64;
         const int64_t k0 = (int64_t)s * BK;
         const int left = (int)(K - k0 < BK ? K - k0 : BK);
-        const gcfloat zero = (gcfloat)f32_tile_zero;
+        const gcfloat zero_a = (gcfloat)f32_tile_zero, zero_b = zero_a + 1;
 #pragma unroll 4
         for (int q = 0; q < 4 * QA; ++q) {
             const int w = q * 256 + t, r = w / BK;
             const int k = 4 * (((w / 4) % CPR) ^ ((r / Cfg::RPB) % CPR)) + w % 4;
-            const gcfloat src = k < left ? a_base + (r < rows ? r : rows - 1) * p.lda + k0 + k : zero;
+            const gcfloat src = k < left ? a_base + (r < rows ? r : rows - 1) * p.lda + k0 + k : zero_a;
             __builtin_amdgcn_global_load_lds((gptr)src, (lptr)(word + q * 256), 4, 0, 0);
         }
 #pragma unroll 4
         for (int q = 0; q < 4 * QB; ++q) {
             const int w = q * 256 + t, k = w / BN;
             const int col = 4 * (((w / 4) % CPB) ^ Cfg::swz_b(k)) + w % 4;
-            const gcfloat src = k < left ? b_base + (k0 + k) * p.ldb + (col < cols ? col : cols - 1) : zero;
+            const gcfloat src = k < left ? b_base + (k0 + k) * p.ldb + (col < cols ? col : cols - 1) : zero_b;
             __builtin_amdgcn_global_load_lds((gptr)src, (lptr)(word + Cfg::ASZ + q * 256), 4, 0, 0);
         }
     };
