@@ -315,7 +315,7 @@ void gemm_direct_kernel(DirectProblem p, int tiles_m, int tiles_n) {
 template <typename Cfg, int WAVES>
 hipError_t launch_direct(const DirectProblem& p, int slices, hipStream_t stream) {
     const int64_t tm = (p.M + Cfg::BM - 1) / Cfg::BM, tn = (p.N + Cfg::BN - 1) / Cfg::BN;
-    if (tm * tn >= (1ll << 31)) return hipErrorInvalidValue;
+    if (!launch_fits(tm * tn, 256 * Cfg::KG)) return hipErrorInvalidValue;
     hipLaunchKernelGGL((gemm_direct_kernel<Cfg, WAVES>), dim3((unsigned)(tm * tn), (unsigned)slices), dim3(256 * Cfg::KG),
                        0, stream, p, (int)tm, (int)tn);
     return hipGetLastError();
@@ -351,7 +351,9 @@ DirectPlan direct_plan(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb
     double least = image;
     for (int big = 0; big < 2; ++big) {
         const int64_t b = big ? 128 : 64;
-        const double tiles = (double)((M + b - 1) / b) * (double)((N + b - 1) / b);
+        const int64_t count = ((M + b - 1) / b) * ((N + b - 1) / b);
+        const double tiles = (double)count;
+        if (!launch_fits(count, x3 ? 512 : 256)) continue;   // (more groups over K run only where tiles are few)
         for (int s = 1; s <= 16 && (s == 1 || (s * 256 <= K && (double)s * mn * 4 <= (double)ws_bytes)); ++s) {
             const int64_t slice = direct_slice(K, s);
             if (slice * (s - 1) >= K) continue;    // every slice non-empty

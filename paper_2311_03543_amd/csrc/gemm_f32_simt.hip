@@ -9,6 +9,7 @@
 //     from a counter as they go (problems sorted by decreasing K, so the
 //     longest tiles go first and the tail is short), with the tile shape
 //     picked per group by the autotuner from kGroupedConfigs.
+#include <cmath>
 #include <type_traits>
 
 #include "common.h"
@@ -142,10 +143,10 @@ int grouped_blocks_per_cu(int config) {
 
 template <typename Cfg, int WAVES>
 hipError_t launch_f32(const F32Problem& p, bool vec, hipStream_t stream) {
-    const int tiles_m = (int)((p.M + Cfg::BM - 1) / Cfg::BM);
-    const int tiles_n = (int)((p.N + Cfg::BN - 1) / Cfg::BN);
-    hipLaunchKernelGGL((gemm_f32_kernel<Cfg, WAVES>), dim3(tiles_m * tiles_n), dim3(256), 0, stream, p, vec, tiles_m,
-                       tiles_n);
+    const int64_t tm = (p.M + Cfg::BM - 1) / Cfg::BM, tn = (p.N + Cfg::BN - 1) / Cfg::BN;
+    if (!launch_fits(tm * tn, 256)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((gemm_f32_kernel<Cfg, WAVES>), dim3((unsigned)(tm * tn)), dim3(256), 0, stream, p, vec, (int)tm,
+                       (int)tn);
     return hipGetLastError();
 }
 
@@ -168,8 +169,8 @@ hipError_t launch_gemm_f32_simt(int64_t M, int64_t N, int64_t K, float alpha, co
     //    64 x  64       17      75   118     129     134      112
     //    32 x  32       29      74
     auto cost = [&](int bm, int bn, double c, double rate) {
-        const double n = (double)((((M + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256);
-        return (n + c) * bm * bn / rate;
+        const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+        return launch_fits(tiles, 256) ? ((double)((tiles + 255) / 256) + c) * bm * bn / rate : INFINITY;
     };
     const double l = cost(128, 256, 0.1, 150), d = cost(128, 128, 0.19, 148), m = cost(64, 64, 0.35, 130),
                  q = cost(32, 32, 0.5, 98);

@@ -202,7 +202,7 @@ void gemm_fp6x3_tile_kernel(Fp6Problem p, int tiles_m, int tiles_n) {
 template <typename Cfg>
 hipError_t launch_tiles(const Fp6Problem& p, int slices, hipStream_t stream) {
     const int64_t tm = (p.M + Cfg::B - 1) / Cfg::B, tn = (p.N + Cfg::B - 1) / Cfg::B;
-    if (tm * tn >= (1ll << 31)) return hipErrorInvalidValue;
+    if (!launch_fits(tm * tn, 256 * Cfg::KG)) return hipErrorInvalidValue;
     static std::atomic<uint64_t> ready{0};
     if (hipError_t e = allow_lds(gemm_fp6x3_tile_kernel<Cfg>, ready, Cfg::SMEM)) return e;
     hipLaunchKernelGGL(gemm_fp6x3_tile_kernel<Cfg>, dim3((unsigned)(tm * tn), (unsigned)slices), dim3(256 * Cfg::KG),
@@ -236,7 +236,7 @@ Fp6x3Plan fp6x3_plan(int64_t M, int64_t N, int64_t Kp, int image_splits) {
     double least = 15 + ceil(tiles(256) * image_splits / 256) * (double)slice_blocks(nkb, image_splits) * 1.25 +
                    reduce(image_splits);
     const auto offer = [&](int tile, int s, double us) {
-        if (us < least) least = us, best = {tile, s};
+        if (us < least && launch_fits((int64_t)tiles(tile == 128 ? 128 : 64), 256)) least = us, best = {tile, s};
     };
     for (int s = 1; s <= image_splits; ++s) {
         const double kb = slice_blocks(nkb, s);

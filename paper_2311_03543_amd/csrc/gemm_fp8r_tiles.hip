@@ -228,7 +228,7 @@ void gemm_fp8r_tile_kernel(Fp8Problem p, int tiles_m, int tiles_n) {
 template <typename Cfg>
 hipError_t launch_tiles(const Fp8Problem& p, int slices, hipStream_t stream) {
     const int64_t tm = (p.M + Cfg::BM - 1) / Cfg::BM, tn = (p.N + Cfg::BN - 1) / Cfg::BN;
-    if (tm * tn >= (1ll << 31)) return hipErrorInvalidValue;
+    if (!launch_fits(tm * tn, Cfg::THREADS * Cfg::KG)) return hipErrorInvalidValue;
     static std::atomic<uint64_t> ready{0};
     if (hipError_t e = allow_lds(gemm_fp8r_tile_kernel<Cfg>, ready, Cfg::SMEM)) return e;
     hipLaunchKernelGGL(gemm_fp8r_tile_kernel<Cfg>, dim3((unsigned)(tm * tn), (unsigned)slices),
@@ -262,7 +262,8 @@ Fp8rPlan fp8r_plan(int64_t M, int64_t N, int64_t Kp, int image_splits) {
     double least = 15 + ceil(tiles(256, 256) * image_splits / 256) *
                             (double)slice_blocks(nkb, image_splits) * kStepNsFp8r * 1e-3 + reduce(image_splits);
     const auto offer = [&](int tile, int s, double us) {
-        if (us < least) least = us, best = {tile, s};
+        if (us < least && (tile == 256 ? launch_fits((int64_t)tiles(256, 128), 512) : launch_fits((int64_t)tiles(64, 64), 256)))
+            least = us, best = {tile, s};
     };
     for (int s = 1; s <= image_splits; ++s) {
         const double kb = slice_blocks(nkb, s);

@@ -11,6 +11,11 @@
 
 namespace cmp {
 
+// Whether a launch of that many workgroups along x is possible: HIP takes fewer
+// than 2^32 threads per dimension.  Products of 2^29 rows or columns pass that
+// with small tiles, so the rules that choose a tile leave out those that do.
+inline bool launch_fits(int64_t workgroups, int threads) { return workgroups <= (int64_t)0xffffffff / threads; }
+
 // ---- FP32 GEMM on the host CPU (host_gemm.cpp) ------------------------------
 // C = alpha * A * B + beta * C over host arrays (beta == 0: C not read), row
 // tiles over at most max_threads threads.  Synchronous.
