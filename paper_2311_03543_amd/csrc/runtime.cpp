@@ -453,14 +453,27 @@ Images images_of(int kind, int64_t M, int64_t N, int64_t K) {
 }
 int image_kind(const Variant& v);
 
+// Whether a call with no slice count forced runs the 256 x 256 tiles over its
+// images, for a shape that has enough of them to go without slices.
+bool runs_image_tiles(int kind, int64_t M, int64_t N, int64_t K, const Images& I) {
+    if (kind == kImgFp8r) return !cmp::fp8r_plan(M, N, I.Kp, 1).tile;
+    if (kind == kImgFp6x3) return !cmp::fp6x3_plan(M, N, I.Kp, 1).tile;
+    return !cmp::direct_plan(M, N, K, K, N, kind == kImgBf16x3 ? 3 : 1, 1, I.total).tile;
+}
+
 // Per-K-block time of one workgroup of an image variant on this device (ns),
 // the price the split-K cost model puts on a K block.  Boards of one product
 // differ by several percent in the clock their power limit allows, so it is
 // taken from this context's own history where possible: over the timed shapes
-// of the variant whose tiles fill every CU (no split) and whose K spans at
-// least 64 blocks, (median time - the operand pre-pass at 5 TB/s) / (tile
-// waves x K blocks), the median over those shapes, kept within [0.75, 1.33]
-// of the constant measured at 8192^3.  Without such a shape, the constant.
+// of the variant whose tiles fill every CU (no split), whose K spans at least
+// 64 blocks and which run these tiles (with another form's time, which is less
+// by up to a fifth, the price came out too low), (median time - the operand
+// pre-pass at 5 TB/s) / (tile waves x K blocks), the median over those shapes,
+// kept within [0.75, 1.33] of the constant measured at 8192^3.  Without such a
+// shape, the constant.  The rules that choose a form compare times fitted with
+// the constants on both sides; with this price on one side only, they would
+// send slow boards to the other forms, and the form of a shape, which is asked
+// for here, would depend on the history itself.
 double step_time(const cmp_ctx* c, int kind) {
     static constexpr double kConst[4] = {cmp::kStepNsBf16, cmp::kStepNsBf16x3, cmp::kStepNsFp8r,
                                          cmp::kStepNsFp6x3};
@@ -478,7 +491,7 @@ double step_time(const cmp_ctx* c, int kind) {
             const Images I = images_of(k, r.M, r.N, r.K);
             const int64_t nkb = (k == kImgBf16 || k == kImgBf16x3 ? I.Kp * 2 : I.Kp) / cmp::kKBlockBytes;
             const int64_t tiles = (I.Mp / cmp::kMfmaTileM) * (I.Np / cmp::kMfmaTileN);
-            if (tiles < cus || nkb < 64) continue;
+            if (tiles < cus || nkb < 64 || !runs_image_tiles(k, r.M, r.N, r.K, I)) continue;
             const double waves = (double)((tiles + cus - 1) / cus);
             const double prepass_ns = (4.0 * (double)(r.M * r.K + r.K * r.N) + (double)I.total) / 5000.0;
             const double t = (double)r.med * 1e6 - prepass_ns;
