@@ -282,8 +282,12 @@ int cmp_reserve(cmp_ctx *ctx, int64_t M, int64_t N, int64_t K);
 int cmp_register_builtin(cmp_ctx *ctx, const char *name, int *id);
 /* Slice count of the 256 x 256 tiles of built-in variant `id` of "gemm" for an
  * M x N x K product under the current setting (1 for f32_simt and for
- * variants registered by the caller): what the workspace is sized for.  With
- * no count forced a call may take smaller tiles and fewer slices. */
+ * variants registered by the caller): what the workspace is sized for.  A call
+ * takes this count where it is forced (cmp_set_split_k) or where it runs these
+ * tiles.  Otherwise it may take another: fp8r and fp6x3 with smaller tiles at
+ * most this one, bf16 and bf16x3 straight from the FP32 operands up to 16, also
+ * where this is 1, their partial sums within the same workspace.
+ * cmp_kernel_stats tells which kernels a call ran. */
 int cmp_split_k(cmp_ctx *ctx, int id, int64_t M, int64_t N, int64_t K, int *splits);
 /* Admissible variants for ctx->tol as a bit mask (bit i = id i). */
 int cmp_admissible(cmp_ctx *ctx, const char *iface, const cmp_context *c, uint64_t *mask);
