@@ -35,7 +35,7 @@ sys.path.insert(0, ROOT)
 import synth  # noqa: E402
 
 PEAK = {  # MI355X published dense peaks (TFLOP/s) and HBM bandwidth (GB/s)
-    "bf16": 2516.6, "fp8": 5033.2, "fp6": 10066.3, "fp32_vector": 157.3, "fp64_vector": 78.6,
+    "bf16": 2516.6, "fp8": 5033.2, "fp6": 10066.3, "fp32_matrix": 157.3, "fp64_vector": 78.6,
     "hbm_gbs": 8000.0,
 }
 BOUNDS = [1e-5, 1e-5, 1e-3, 1e-2]
@@ -50,7 +50,7 @@ def kernel_roofline(name: str, M: int, N: int, K: int):
     Kp64 = -(-K // 64) * 64
     Kp128 = -(-K // 128) * 128
     if name == "gemm_f32_simt":
-        return "alu", 2.0 * M * N * K, PEAK["fp32_vector"], "TFLOP/s"
+        return "mfma", 2.0 * M * N * K, PEAK["fp32_matrix"], "TFLOP/s"
     if name in ("gemm_bf16_tn", "gemm_bf16_direct"):
         return "mfma", 2.0 * M * N * K, PEAK["bf16"], "TFLOP/s"
     if name in ("gemm_bf16x3_tn", "gemm_bf16x3_direct"):
@@ -85,11 +85,23 @@ KERNEL_SOURCES = {  # kernel name -> source file (relative to the repo root)
 }
 
 
+def kernel_headers(name: str):
+    """The headers that hold parts of a kernel (relative to the repo root)."""
+    own = ["f32_tile.h"] if name == "gemm_f32_simt" else ["mfma_tile.h"]
+    return [f"paper_2311_03543_amd/csrc/{h}" for h in own + ["common.h"]]
+
+
 def measured_traffic(name: str, n: int):
     """HBM bytes per launch of kernel `name` at M = N = K = n from the committed counter summary
     (FETCH_SIZE and WRITE_SIZE per dispatch, each scaled by the factor a plain copy of known size
-    gives), or None when there is none or the kernel source changed since it was taken."""
+    gives), or None when there is none or the kernel's source or one of its headers changed since
+    it was taken."""
     import hashlib
+
+    def digest(rel):
+        with open(os.path.join(ROOT, rel), "rb") as f:
+            return hashlib.sha256(f.read()).hexdigest()
+
     path = os.path.join(ROOT, "profiles", f"hbm_traffic_n{n}.json")
     src = KERNEL_SOURCES.get(name)
     if not src or not os.path.exists(path):
@@ -98,10 +110,12 @@ def measured_traffic(name: str, n: int):
         rec = json.load(f).get("kernels", {}).get(name)
     if not rec:
         return None
-    with open(os.path.join(ROOT, src), "rb") as f:
-        digest = hashlib.sha256(f.read()).hexdigest()
-    if rec.get("source_sha256") != digest:
+    if rec.get("source_sha256") != digest(src):
         return None
+    headers = rec.get("headers_sha256", {})
+    for h in kernel_headers(name):
+        if os.path.exists(os.path.join(ROOT, h)) and headers.get(h) != digest(h):
+            return None
     return rec.get("hbm_bytes_per_launch")
 
 
