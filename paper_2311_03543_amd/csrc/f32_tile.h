@@ -97,7 +97,7 @@ __device__ __forceinline__ void f32_stage_wait() {
 }
 __device__ __forceinline__ void f32_stage_barrier() {
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(63 & 15 | (3 << 14) | (7 << 4));   // lgkmcnt(0): own LDS reads done
+    __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));   // lgkmcnt(0): own LDS reads done
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 }

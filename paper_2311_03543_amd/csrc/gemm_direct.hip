@@ -47,15 +47,16 @@ struct DirectProblem {
     int64_t slice;    // K values per slice (a multiple of 32)
 };
 
-template <int BM_, int BN_, int NT_, int KG_, int PF_ = 2>
+template <int BM_, int BN_, int NT_, int KG_>
 struct DirectCfg {
-    static constexpr int BM = BM_, BN = BN_, NT = NT_, KG = KG_, PF = PF_;
+    static constexpr int BM = BM_, BN = BN_, NT = NT_, KG = KG_;
+    static constexpr int PF = 2;                                 // stages in flight in registers (3 or 4: no faster, or spills)
     static constexpr int BK = 32, NL = NT == 3 ? 2 : 1;          // levels: hi, lo
     static constexpr int MI = BM / 64, NJ = BN / 64;             // 32 x 32 blocks per wave
     static constexpr int UA = BM / 32, UB = BN / 64;             // units per thread and stage: 4 values of A, 8 of B
     static constexpr int SLAB_A = BM * 64, SLAB_B = BN * 64;     // bytes of one level
     static constexpr int STAGE = NL * (SLAB_A + SLAB_B);
-    static constexpr int U = PF % 2 ? 2 * PF : PF;               // stages per unrolled pass: register sets and LDS halves
+    static constexpr int U = PF;                                 // stages per unrolled pass: register sets and LDS halves
     static_assert(BM % 64 == 0 && BN % 64 == 0 && (NT == 1 || NT == 3), "tile");
     static_assert(KG == 1 || KG == 2 || KG == 4, "each group finishes its share of the accumulators");
     // LDS: each group's two stages; after the main loop the groups' accumulators
@@ -362,7 +363,7 @@ DirectPlan direct_plan(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb
                                                : (x3 ? 4 + (n + 0.64) * 0.0081 * k : 4 + (n + 0.87) * 0.0047 * k));
             if (us < least) {
                 least = us;
-                best = {big ? (n > 1 && !x3 ? 127 : 128) : tiles * s <= 256 ? 63 : 64, s};
+                best = {big ? (n > 1 && !x3 ? 127 : 128) : x3 && tiles * s <= 256 ? 63 : 64, s};
             }
         }
     }

@@ -151,10 +151,10 @@ hipError_t launch_gemm_bf16_tn(int64_t M, int64_t N, int64_t Kp, int nterms, flo
                                hipStream_t stream);
 // The same product straight from the FP32 operands, without images
 // (gemm_direct.hip), where that is expected to be faster: tile 0 = use the
-// images; otherwise the tile (128, or 127: 128 with one group over K; 64, or 63:
-// 64 with more groups over K) and the K slices (> 1: slice s writes its raw sum
-// to partial + s * M * N, as above).  image_splits: the slices the image form
-// would take; ws_bytes: room for partial sums.
+// images; otherwise the tile (128, or 127: 128 with one group over K; 64, or for
+// three terms 63: 64 with more groups over K) and the K slices (> 1: slice s
+// writes its raw sum to partial + s * M * N, as above).  image_splits: the
+// slices the image form would take; ws_bytes: room for partial sums.
 struct DirectPlan {
     int tile = 0, slices = 1;
 };
