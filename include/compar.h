@@ -498,13 +498,15 @@ int cmp_prepass_images(cmp_ctx *ctx, int id, const cmp_gemm_args *args, void *ou
 
 /* A plan runs `count` independent gemm problems (each problem's own alpha,
  * beta and leading dimensions; device pointers owned by the caller and fixed
- * for the plan's lifetime) as ONE persistent kernel whose
- * workgroups take tiles of the concatenated tile list from a device counter
- * as they finish their previous one, problems ordered by decreasing K (the
- * longest tiles first).  Each launch leaves the plan's counters zero for the
- * next one (no memset, so it can be captured), and two
- * launches of one plan must not run at the same time (they would share the
- * counters and the problems' C).  A configuration is a tile shape and an
+ * for the plan's lifetime) as ONE persistent kernel whose workgroups claim
+ * tiles from device counters as they go, the longest tiles (largest K) first:
+ * the FP32 configurations from eight lists, one per XCD, balanced by work, and
+ * from the others once the own one is empty; the bf16x3 configuration from one
+ * list.  Each launch leaves the plan's counters zero for the next one (no
+ * memset, so it can be captured).  Two launches of one plan must not run at
+ * the same time: they share the counters and the problems' C, and may leave
+ * tiles out or compute them twice; launches after them are right again.  A
+ * configuration is a tile shape and an
  * arithmetic, one of cmp_grouped_config_count(): the first ones are FP32
  * tiles, bit-identical to cmp_gemm_variant with "f32_simt" per problem; the
  * last one runs the "bf16x3" variant's arithmetic (one launch splitting every

@@ -127,7 +127,8 @@ __device__ __forceinline__ int wave_find_last(int count, int value, F&& start) {
 // list's counter, and from the other lists' once the own one is empty.
 // `counters` holds one 32-bit counter per list and one of the workgroups that
 // are done, kQueuePitch words apart, zero before the first launch; the last
-// workgroup zeroes them for the next one (a kernel that did took 4.6 us).
+// workgroup leaves them zero for the next one (a kernel that zeroed them took
+// 4.6 us).
 struct TileQueues {
     int start[kXcds + 1];
 };

@@ -4,11 +4,13 @@
 // Two launch forms share the tile code of f32_tile.h:
 //   - one problem: a tile per workgroup, tiles renumbered so each XCD works
 //     on a contiguous, L2-friendly block of C;
-//   - a group of problems of uneven shapes: one persistent launch whose
-//     workgroups claim tiles of the concatenated tile list of all problems
-//     from a counter as they go (problems sorted by decreasing K, so the
-//     longest tiles go first and the tail is short), with the tile shape
-//     picked per group by the autotuner from kGroupedConfigs.
+//   - a group of problems of uneven shapes: one persistent launch over eight
+//     tile lists, one per XCD, with a counter each (common.h, TileQueues).  A
+//     workgroup claims its next tile ahead of the stores of the current one
+//     (64 x 64 tiles: at its start), and from the other lists once its own is
+//     empty.  Lists hold whole problems where they can, balanced by work, in
+//     decreasing order of K, so the longest tiles go first and the tail is
+//     short.  The autotuner picks the tile shape per group from kGroupedConfigs.
 #include <cmath>
 #include <type_traits>
 

@@ -226,7 +226,8 @@ int slice_blocks(int nkb, int slices) { return (nkb + slices - 1) / slices; }
 // between two groups of waves only while there is one (128 x 100 x 2000: 9.8 us,
 // undivided 11.5; 2048^3 29.9 and 28.5).  128 x 128 tiles end together, so their
 // stores are not hidden (2000^2 x 200: 17.4 us, 64 x 64 tiles 12); their third ring
-// slot saves a wait for HBM (300 x 4000 x 8191: 81 -> 49 us).
+// slot saves a wait for HBM (300 x 4000 x 8191: 81 -> 49 us).  The 256 x 256 tiles'
+// 1.25 us per K block is the fit over these shapes (kStepNsFp6x3 is 8192^3).
 Fp6x3Plan fp6x3_plan(int64_t M, int64_t N, int64_t Kp, int image_splits) {
     const int nkb = (int)(Kp / 64);
     const double mn = (double)M * (double)N, bytes_per_us = 5e6;
